@@ -45,14 +45,11 @@
 // masked), both further down.
 #include <type_traits>
 
-#include "device_common.h"
-#include "launch.h"
+#include "gemm_common.h"
 #include "plan_device.h"
 
 namespace rag {
 namespace {
-
-typedef __attribute__((address_space(3))) void lds_void_t;
 
 constexpr int BN = 256, BK = 32;
 constexpr int WN = 64, FN = WN / 32;        // wave tile: all BM tokens x WN features
@@ -60,7 +57,6 @@ constexpr int KSTEPS = BK / 16;             // MFMA k-steps per K step
 constexpr int kChunks = BK / 8;             // 16-byte chunks per LDS row
 constexpr int kRowsPerBlock = 64 / kChunks; // rows filled by one 1 KB wave copy
 constexpr int kEpiRows = 32;                // tokens per epilogue slice
-constexpr int kGroupM = 8;                  // token tiles per group in the tile order
 
 // Tile configuration: BM tokens x BN features per workgroup of 4 waves, wave w
 // holding all BM tokens x features [64 w, 64 w + 64); BM = 128, or 64 for the
@@ -100,10 +96,6 @@ constexpr int tile_lds_bytes() { return pair_w(W_KN, TRI) ? Cfg<BM>::kPairLdsByt
 // bank groups.
 __device__ __forceinline__ int swz(int row) { return (row >> 2) & (kChunks - 1); }
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
-}
-
 // Per-lane byte offset for copying a block of kRowsPerBlock rows starting at
 // row0: lane l fills LDS slot l (row row0 + l / kChunks, physical chunk
 // l % kChunks) and so reads the logical chunk that the swizzle maps there.
@@ -116,13 +108,6 @@ __device__ __forceinline__ int copy_voffset(int lane, int row0, int ld_bytes) {
 // wave-uniform and travels in the scalar offset.
 __device__ __forceinline__ void copy_block(__amdgpu_buffer_rsrc_t rsrc, uint16_t* dst, int voff, int k0b) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_t*)dst, 16, voff, k0b, 0, 0);
-}
-
-// Workgroup barrier that waits for LDS traffic but not for the copies still in
-// flight (a __syncthreads() fence would drain them all): the caller has already
-// waited for the copies it needs.
-__device__ __forceinline__ void barrier_lds() {
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 __device__ __forceinline__ bf16x8 lds_frag(const uint16_t* tile, int row, int chunk) {
@@ -138,18 +123,9 @@ constexpr int kKnChunks = BN / 8;
 constexpr int kKnRowsPerBlock = 64 / kKnChunks;  // rows one 1 KB wave copy fills
 __device__ __forceinline__ int swz_kn(int row) { return (row & 3) << 2; }
 
-// Paired-w stages: BN rows of 2 BK (128 bytes, eight 16-byte chunks) whose chunk
-// index is XOR-swizzled with bits 1-3 of the row, so the fragment reads of 16
-// consecutive rows (two rows per 256-byte bank line) hit 16 distinct bank groups.
-// A 1 KB wave copy fills 8 whole rows, so every copy request is a full 128-byte
-// line: half as many L2 requests as 64-byte K-step rows.
-__device__ __forceinline__ int swz2(int row) { return (row >> 1) & 7; }
-
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
+// Paired-w stages: BN rows of 2 BK (128 bytes), chunks swizzled by swz2.  A 1 KB wave
+// copy fills 8 whole rows, so every copy request is a full 128-byte line: half as
+// many L2 requests as 64-byte K-step rows.
 typedef __attribute__((ext_vector_type(4))) short short4_t;
 typedef __attribute__((address_space(3))) short4_t lds_short4_t;
 
@@ -161,25 +137,6 @@ __device__ __forceinline__ bf16x8 lds_frag_tr(const uint16_t* lo_addr, const uin
     const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_t*)lo_addr));
     const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4_t*)hi_addr));
     return as_bf16x8(u32x4{lo[0], lo[1], hi[0], hi[1]});
-}
-
-// Output tile of a linear workgroup id.  Workgroups are dealt to the 8 XCDs
-// round-robin, so the id is first remapped to give each XCD a contiguous range.
-// That range is walked in groups of kGroupM token tiles, token tile fastest, so
-// the tiles an XCD runs at once share both x rows and w rows in its L2 (groups of
-// 2 to 16 measured alike on the layer's GEMMs except FF1, slower below 8).
-__device__ __forceinline__ void group_walk(int t, int tiles_m, int tiles_n, int& tm, int& tn) {
-    const int gsz = kGroupM * tiles_n, first = (t / gsz) * kGroupM;
-    const int gm = min(tiles_m - first, kGroupM);
-    tm = first + (t % gsz) % gm;
-    tn = (t % gsz) / gm;
-}
-
-__device__ __forceinline__ void tile_coords(int bid, int nblocks, int tiles_m, int tiles_n, int& tm, int& tn) {
-    const int per = nblocks / 8, rem = nblocks % 8;
-    const int xcd = bid % 8, idx = bid / 8;
-    const int t = xcd < rem ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
-    group_walk(t, tiles_m, tiles_n, tm, tn);
 }
 
 // Wait until at most `n` copy instructions of this wave are outstanding (the
@@ -696,241 +653,6 @@ void k_gemm_bf16_dual(const uint16_t* __restrict__ x, int ldx, const uint16_t* _
                                                                 tm * 64, tn * BN, smem);
 }
 
-// fp32: 64x64 tiles, K step 16, 4x4 outputs per thread, plain FMA.
-template <int ACT>
-__device__ __forceinline__ void gemm_tile_f32(const float* __restrict__ x, int ldx, const float* __restrict__ w,
-                                              const float* __restrict__ bias, const float* residual, int ldr,
-                                              float* y, int ldy, int T, int K, int N, int m0, int n0) {
-    __shared__ float xs[16][64 + 1], ws[16][64 + 1];
-    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        __syncthreads();
-        for (int e = threadIdx.x; e < 64 * 16; e += 256) {
-            const int r = e / 16, c = e % 16;
-            const int k = k0 + c;
-            xs[c][r] = (m0 + r < T && k < K) ? x[(int64_t)(m0 + r) * ldx + k] : 0.f;
-            ws[c][r] = (n0 + r < N && k < K) ? w[(int64_t)(n0 + r) * K + k] : 0.f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            float a[4], b[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                a[u] = xs[c][ty * 4 + u];
-                b[u] = ws[c][tx + 16 * u];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[u][v] = fmaf(a[u], b[v], acc[u][v]);
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int m = m0 + ty * 4 + u;
-        if (m >= T) continue;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int n = n0 + tx + 16 * v;
-            if (n >= N) continue;
-            float o = acc[u][v] + (bias ? bias[n] : 0.f);
-            o = activate<ACT>(o);
-            if (residual) o += residual[(int64_t)m * ldr + n];
-            y[(int64_t)m * ldy + n] = o;
-        }
-    }
-}
-
-template <int ACT>
-__global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ x, int ldx, const float* __restrict__ w,
-                                                   const float* __restrict__ bias, const float* residual, int ldr,
-                                                   float* y, int ldy, int T, int K, int N) {
-    gemm_tile_f32<ACT>(x, ldx, w, bias, residual, ldr, y, ldy, T, K, N, blockIdx.x * 64, blockIdx.y * 64);
-}
-
-// fp32 on the matrix cores: v_mfma_f32_32x32x2f32 (fp32 products and fp32
-// accumulation, as the VALU kernel above).  128 x 128 output tiles, four waves
-// of 64 x 64; operands go global -> LDS with bounds-checked buffer loads (rows
-// past T or N read as zeros) into two stages of 32 k, 128-byte rows whose
-// 16-byte chunks are XOR-swizzled like the bf16 paired-w rows.  In MFMA step s
-// of an 8-k group a lane supplies k = 4 (lane / 32) + s (the same k order for
-// both operands), so one 16-byte LDS read feeds four MFMAs.  The MFMA computes
-// C^T = W X^T: a lane holds four consecutive output features of one token,
-// stored as one 16-byte vector.
-constexpr int kF32K = 32;
-template <int TS>
-constexpr int f32_stage_floats() { return 2 * TS * kF32K; }  // TS x rows, then TS w rows
-
-// TS = 128 (four waves of 64 x 64) or, for launches that would leave most CUs
-// idle, TS = 64 (four waves of 32 x 32: four times the tiles; a wave's single
-// accumulator chain still issues an fp32 MFMA every cycle the pipe allows).
-template <int ACT, bool HB, bool HR, int TS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void k_gemm_f32_mfma(const float* __restrict__ x, int ldx, const float* __restrict__ w,
-                     const float* __restrict__ bias, const float* residual, int ldr, float* y, int ldy, int T,
-                     int K, int N, int tiles_m, int tiles_n) {
-    static_assert(TS == 128 || TS == 64, "tile side");
-    constexpr int WS = TS / 2, F = WS / 32;          // the wave's sub-tile side and 32-wide blocks
-    constexpr int kStage = f32_stage_floats<TS>();
-    constexpr int kBx = TS / 8, kPerWave = 2 * kBx / 4;  // 1 KB x blocks; copies per wave and step
-    extern __shared__ __attribute__((aligned(16))) float fsm[];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
-    const int l32 = lane % 32, h2 = lane / 32;
-    const int wm = wave >> 1, wn = wave & 1;  // the wave's WS tokens and WS features
-    int tm, tn;
-    tile_coords(blockIdx.x, gridDim.x, tiles_m, tiles_n, tm, tn);
-    const int m0 = tm * TS, n0 = tn * TS;
-    const __amdgpu_buffer_rsrc_t rx = make_rsrc(x + (int64_t)m0 * ldx, (uint32_t)min(T - m0, TS) * ldx * 4u);
-    const __amdgpu_buffer_rsrc_t rw = make_rsrc(w + (int64_t)n0 * K, (uint32_t)min(N - n0, TS) * K * 4u);
-    // copy block b (1 KB: 8 rows of 128 bytes; blocks 0 .. kBx - 1 x rows, then w rows):
-    // this wave fills blocks kPerWave wave .. + kPerWave - 1, lane l slot l (row 8 b' + l / 8,
-    // physical chunk l % 8, which holds logical chunk (l % 8) ^ swz2(row))
-    int voff[8];  // first kPerWave used (a size that depends on TS made hipcc drop the host stub)
-#pragma unroll
-    for (int i = 0; i < kPerWave; ++i) {
-        const int blk = wave * kPerWave + i, bl = blk % kBx, row = bl * 8 + lane / 8;
-        voff[i] = row * (blk < kBx ? ldx : K) * 4 + ((lane % 8) ^ swz2(row)) * 16;
-    }
-    auto issue = [&](int step) {
-        float* st = fsm + (step & 1) * kStage;
-#pragma unroll
-        for (int i = 0; i < kPerWave; ++i) {
-            const int blk = wave * kPerWave + i;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(blk < kBx ? rx : rw, (lds_void_t*)(st + blk * 256), 16, voff[i],
-                                                     step * kF32K * 4, 0, 0);
-        }
-    };
-    floatx16 acc[F][F];
-#pragma unroll
-    for (int i = 0; i < F; ++i)
-#pragma unroll
-        for (int j = 0; j < F; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    const int nk = K / kF32K;
-    issue(0);
-    for (int k = 0; k < nk; ++k) {
-        wait_vm<0>();
-        barrier_lds();  // step k's stage is visible; the other stage is no longer read
-        if (k + 1 < nk) issue(k + 1);
-        const float* xs = fsm + (k & 1) * kStage;
-        const float* ws = xs + TS * kF32K;
-#pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-            floatx4 a[F], bq[F];
-#pragma unroll
-            for (int i = 0; i < F; ++i) {
-                const int r = wn * WS + i * 32 + l32;
-                a[i] = *reinterpret_cast<const floatx4*>(ws + r * kF32K + (((gq * 2 + h2) ^ swz2(r)) * 4));
-            }
-#pragma unroll
-            for (int j = 0; j < F; ++j) {
-                const int r = wm * WS + j * 32 + l32;
-                bq[j] = *reinterpret_cast<const floatx4*>(xs + r * kF32K + (((gq * 2 + h2) ^ swz2(r)) * 4));
-            }
-#pragma unroll
-            for (int st = 0; st < 4; ++st)
-#pragma unroll
-                for (int i = 0; i < F; ++i)
-#pragma unroll
-                    for (int j = 0; j < F; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][st], bq[j][st], acc[i][j], 0, 0, 0);
-        }
-    }
-    // acc[i][j][4g + r]: token wm*WS + j*32 + l32, feature wn*WS + i*32 + 8g + 4 h2 + r.
-    // The bias groups, and per 32-feature block the residual chunks, are loaded
-    // before their first use (indexes clamped into range; one wait for each batch):
-    // loaded under the range tests, each was waited for before the next was issued.
-    floatx4 bv[F][4];
-#pragma unroll
-    for (int i = 0; i < F; ++i)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            bv[i][g] = floatx4{0.f, 0.f, 0.f, 0.f};
-            if constexpr (HB) bv[i][g] = *reinterpret_cast<const floatx4*>(bias + min(n0 + wn * WS + i * 32 + 8 * g + 4 * h2, N - 4));
-        }
-#pragma unroll
-    for (int i = 0; i < F; ++i) {
-        floatx4 rv[4][F];
-        if constexpr (HR) {
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-#pragma unroll
-                for (int j = 0; j < F; ++j)
-                    rv[g][j] = *reinterpret_cast<const floatx4*>(
-                        residual + (int64_t)min(m0 + wm * WS + j * 32 + l32, T - 1) * ldr +
-                        min(n0 + wn * WS + i * 32 + 8 * g + 4 * h2, N - 4));
-        }
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int n = n0 + wn * WS + i * 32 + 8 * g + 4 * h2;
-            if (n >= N) continue;
-#pragma unroll
-            for (int j = 0; j < F; ++j) {
-                const int m = m0 + wm * WS + j * 32 + l32;
-                if (m >= T) continue;
-                floatx4 o;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) o[r] = activate<ACT>(acc[i][j][4 * g + r] + bv[i][g][r]);
-                if constexpr (HR) o += rv[g][j];
-                *reinterpret_cast<floatx4*>(y + (int64_t)m * ldy + n) = o;
-            }
-        }
-    }
-}
-
-template <int ACT, bool HB, bool HR, int TS>
-hipError_t launch_f32_mfma_ts(const float* x, int ldx, const float* w, const float* bias, const float* residual,
-                              int ldr, float* y, int ldy, int T, int K, int N, hipStream_t s) {
-    constexpr int kLds = 2 * f32_stage_floats<TS>() * 4;
-    static bool attr_set = false;  // benign race: every thread sets the same value
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_f32_mfma<ACT, HB, HR, TS>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
-    const int tiles_m = (T + TS - 1) / TS, tiles_n = (N + TS - 1) / TS;
-    hipLaunchKernelGGL((k_gemm_f32_mfma<ACT, HB, HR, TS>), dim3(tiles_m * tiles_n), dim3(256), kLds, s, x, ldx, w,
-                       bias, residual, ldr, y, ldy, T, K, N, tiles_m, tiles_n);
-    return hipGetLastError();
-}
-
-// 64 x 64 tiles when they cut the busiest CU's share of work, counted in rounds of
-// one tile per CU (a 128 x 128 tile being four 64 x 64 ones), by a fifth or more:
-// they re-read each operand twice as often, which large launches notice (35475 x
-// 1024 x 4096: 139 rounds of 64 x 64 against 35 of 128 x 128 ran 7% slower)
-template <int ACT, bool HB, bool HR>
-hipError_t launch_f32_mfma(const float* x, int ldx, const float* w, const float* bias, const float* residual, int ldr,
-                           float* y, int ldy, int T, int K, int N, hipStream_t s) {
-    const int64_t cus = device_cu_count();
-    const int64_t tiles128 = (int64_t)((T + 127) / 128) * ((N + 127) / 128);
-    const int64_t tiles64 = (int64_t)((T + 63) / 64) * ((N + 63) / 64);
-    if (5 * ((tiles64 + cus - 1) / cus) <= 16 * ((tiles128 + cus - 1) / cus))
-        return launch_f32_mfma_ts<ACT, HB, HR, 64>(x, ldx, w, bias, residual, ldr, y, ldy, T, K, N, s);
-    return launch_f32_mfma_ts<ACT, HB, HR, 128>(x, ldx, w, bias, residual, ldr, y, ldy, T, K, N, s);
-}
-
-template <int ACT>
-hipError_t launch_f32_mfma_act(const float* x, int ldx, const float* w, const float* bias, const float* residual,
-                               int ldr, float* y, int ldy, int T, int K, int N, hipStream_t s) {
-    if (bias && residual) return launch_f32_mfma<ACT, true, true>(x, ldx, w, bias, residual, ldr, y, ldy, T, K, N, s);
-    if (bias) return launch_f32_mfma<ACT, true, false>(x, ldx, w, bias, residual, ldr, y, ldy, T, K, N, s);
-    if (residual) return launch_f32_mfma<ACT, false, true>(x, ldx, w, bias, residual, ldr, y, ldy, T, K, N, s);
-    return launch_f32_mfma<ACT, false, false>(x, ldx, w, bias, residual, ldr, y, ldy, T, K, N, s);
-}
-
-// The matrix-core fp32 kernel needs whole 32-k steps, 16-byte vectors (rows of x,
-// w, y and residual and the bias 16-byte aligned) and N % 4 == 0.
-bool f32_mfma_ok(const void* x, int ldx, const void* w, const void* bias, const void* residual, int ldr,
-                 const void* y, int ldy, int K, int N) {
-    auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-    return K % kF32K == 0 && N % 4 == 0 && ldx % 4 == 0 && ldy % 4 == 0 && al(x) && al(w) && al(y) &&
-           (!bias || al(bias)) && (!residual || (al(residual) && ldr % 4 == 0));
-}
-
 // ---------------------------------------------------------------------------
 // Variable-sized batched GEMM: one workgroup per entry of the plan's tile list
 // (problems largest first).  The workgroup -> entry map deals the list to the
@@ -942,68 +664,9 @@ bool f32_mfma_ok(const void* x, int ldx, const void* w, const void* bias, const 
 constexpr int kVgemmChunk = 32;
 constexpr int kVgemmGridQuantum = 8 * kVgemmChunk;  // the grid is a multiple of this
 
-struct VgemmArgs {
-    const int32_t* dims;
-    const int64_t* a_off;
-    const int64_t* b_off;
-    const int64_t* c_off;
-    const int4* items;
-    int32_t* status;
-    int batch;
-    int64_t a_cap, b_cap, c_cap;
-};
-
-// The status word may be written in these kernels (atomicOr), so the compiler
-// cannot keep the plan reads in scalar registers by itself; these are
-// workgroup-uniform and are made so explicitly (otherwise every buffer
-// descriptor built from them becomes a per-lane loop).
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ int64_t uni64(int64_t v) {
-    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
-    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(static_cast<uint64_t>(v) >> 32));
-    return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
-}
-
-// The tile one workgroup computes: problem p, output rows [m0, m0 + 128) and
-// columns [n0, n0 + 256) of C_p = A_p B_p^T.
-struct VgemmTile {
-    int m, n, k, m0, n0;
-    int64_t a_off, b_off, c_off;
-};
-
-__device__ __forceinline__ VgemmTile vgemm_tile(const VgemmArgs& va, int e) {
-    const int4 it = va.items[e];
-    const int p = uni(it.x);
-    VgemmTile t;
-    t.m = uni(va.dims[3 * p]);
-    t.n = uni(va.dims[3 * p + 1]);
-    t.k = uni(va.dims[3 * p + 2]);
-    t.m0 = uni(it.y) * kVgemmTileM;
-    t.n0 = uni(it.z) * kVgemmTileN;
-    t.a_off = uni64(va.a_off[p]);
-    t.b_off = uni64(va.b_off[p]);
-    t.c_off = uni64(va.c_off[p]);
-    return t;
-}
-
 __device__ __forceinline__ int vgemm_entry(int bid) {
     const int xcd = bid % 8, idx = bid / 8;
     return ((idx / kVgemmChunk) * 8 + xcd) * kVgemmChunk + idx % kVgemmChunk;
-}
-
-// False if the plan reports a data error or this call cannot run on it; one
-// thread then records why and every workgroup returns.
-__device__ __forceinline__ bool vgemm_ok(const VgemmArgs& va, bool bf16) {
-    if (va.status[0] != 0) return false;
-    int bad = 0;
-    if (va.a_off[va.batch] > va.a_cap || va.b_off[va.batch] > va.b_cap || va.c_off[va.batch] > va.c_cap)
-        bad |= kVgemmOperandCap;
-    if (bf16 && va.status[2] != 0) bad |= kVgemmBf16Shape;
-    if (bad) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(va.status, bad);
-        return false;
-    }
-    return true;
 }
 
 // C = 0 over the rows [m0, m) x columns [n0, n) of a tile (problems with k = 0).
@@ -1031,20 +694,6 @@ void k_vgemm_bf16(VgemmArgs va, const uint16_t* __restrict__ a, const uint16_t* 
                                                  t.k, t.n, t.m0, t.n0, smem);
 }
 
-// fp32: the 128 x 256 tile as eight 64 x 64 sub-tiles of the fp32 GEMM.
-__global__ __launch_bounds__(256) void k_vgemm_f32(VgemmArgs va, const float* __restrict__ a,
-                                                    const float* __restrict__ b, float* c) {
-    if (!vgemm_ok(va, false)) return;
-    const int e = vgemm_entry(blockIdx.x);
-    if (e >= uni(va.status[1])) return;
-    const VgemmTile t = vgemm_tile(va, e);
-    for (int sub = 0; sub < (kVgemmTileM / 64) * (kVgemmTileN / 64); ++sub) {
-        const int sm = t.m0 + (sub % (kVgemmTileM / 64)) * 64, sn = t.n0 + (sub / (kVgemmTileM / 64)) * 64;
-        if (sm < t.m && sn < t.n)
-            gemm_tile_f32<0>(a + t.a_off, t.k, b + t.b_off, nullptr, nullptr, 0, c + t.c_off, t.n, t.m, t.k, t.n, sm, sn);
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Triangular matrix multiplication C = tril(L) B (trmm; Section 7.1): L is
 // n x n, B and C are n x m, all row-major.  The reduction over k is a variable
@@ -1054,20 +703,6 @@ __global__ __launch_bounds__(256) void k_vgemm_f32(VgemmArgs va, const float* __
 // ---------------------------------------------------------------------------
 constexpr int kTrmmTile = 128;  // output rows per tile (the BM = 128 GEMM tile)
 
-
-// Tiles are listed heaviest row first, columns ascending, and dealt to the XCDs
-// in chunks of `chunk` consecutive columns (workgroups go to the XCDs
-// round-robin).  With chunk = tiles_n / 8 each XCD owns the same column panels
-// of B in every row (so B is fetched into one L2, not eight) and gets the same
-// share of every row, hence the same total work.
-__device__ __forceinline__ bool trmm_tile_coords(int bid, int tiles_m, int tiles_n, int chunk, int& tm, int& tn) {
-    const int xcd = bid % 8, idx = bid / 8;
-    const int t = ((idx / chunk) * 8 + xcd) * chunk + idx % chunk;
-    if (t >= tiles_m * tiles_n) return false;
-    tm = tiles_m - 1 - t / tiles_n;
-    tn = t % tiles_n;
-    return true;
-}
 
 __global__ __launch_bounds__(Cfg<kTrmmTile>::kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_trmm_bf16(const uint16_t* __restrict__ l, int ldl, const uint16_t* __restrict__ b, int ldb, uint16_t* c,
@@ -1079,51 +714,6 @@ void k_trmm_bf16(const uint16_t* __restrict__ l, int ldl, const uint16_t* __rest
     const int k_end = min(m0 + kTrmmTile, (n + 63) & ~63);  // a multiple of 64; L and B past n read as zeros
     gemm_tile_bf16<kTrmmTile, 0, false, false, true, true>(l, ldl, b, nullptr, nullptr, 0, c, ldc, n, k_end, m, m0,
                                                             tn * BN, smem, ldb, n);
-}
-
-// fp32: 64 x 64 tiles of plain FMA, the reduction stopping at the tile's last row
-// and L entries past the diagonal read as zero.
-__global__ __launch_bounds__(256) void k_trmm_f32(const float* __restrict__ l, int ldl, const float* __restrict__ b,
-                                                   int ldb, float* c, int ldc, int n, int m) {
-    __shared__ float ls[16][64 + 1], bs[16][64 + 1];
-    const int tiles_m = (n + 63) / 64;
-    const int m0 = (tiles_m - 1 - (int)blockIdx.x) * 64, n0 = blockIdx.y * 64;  // heaviest rows first
-    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-    const int k_end = min(m0 + 64, n);
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < k_end; k0 += 16) {
-        __syncthreads();
-        for (int e = threadIdx.x; e < 64 * 16; e += 256) {
-            const int r = e / 16, cc = e % 16, k = k0 + cc;
-            ls[cc][r] = (m0 + r < n && k <= m0 + r) ? l[(int64_t)(m0 + r) * ldl + k] : 0.f;
-            const int kr = k0 + e / 64, col = n0 + e % 64;
-            bs[e / 64][e % 64] = (kr < n && col < m) ? b[(int64_t)kr * ldb + col] : 0.f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int cc = 0; cc < 16; ++cc) {
-            float av[4], bv[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                av[u] = ls[cc][ty * 4 + u];
-                bv[u] = bs[cc][tx + 16 * u];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[u][v] = fmaf(av[u], bv[v], acc[u][v]);
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int i = m0 + ty * 4 + u;
-        if (i >= n) continue;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int j = n0 + tx + 16 * v;
-            if (j < m) c[(int64_t)i * ldc + j] = acc[u][v];
-        }
-    }
 }
 
 template <int ACT, bool HB, bool HR>
@@ -1198,8 +788,8 @@ hipError_t launch_vgemm(const VgemmView& p, int dtype, const void* a, int64_t a_
         hipLaunchKernelGGL(k_vgemm_bf16, dim3((unsigned)grid), dim3(C::kThreads), kLds, s, va,
                            static_cast<const uint16_t*>(a), static_cast<const uint16_t*>(b), static_cast<uint16_t*>(c));
     } else {
-        hipLaunchKernelGGL(k_vgemm_f32, dim3((unsigned)grid), dim3(256), 0, s, va, static_cast<const float*>(a),
-                           static_cast<const float*>(b), static_cast<float*>(c));
+        return launch_vgemm_f32(va, p.tile_cap, static_cast<const float*>(a), static_cast<const float*>(b),
+                                static_cast<float*>(c), s);
     }
     return hipGetLastError();
 }
@@ -1224,9 +814,8 @@ hipError_t launch_trmm(int dtype, const void* l, int ldl, const void* b, int ldb
                            static_cast<const uint16_t*>(l), ldl, static_cast<const uint16_t*>(b), ldb,
                            static_cast<uint16_t*>(c), ldc, n, m, tiles_m, tiles_n);
     } else {
-        hipLaunchKernelGGL(k_trmm_f32, dim3((n + 63) / 64, (m + 63) / 64), dim3(256), 0, s,
-                           static_cast<const float*>(l), ldl, static_cast<const float*>(b), ldb, static_cast<float*>(c),
-                           ldc, n, m);
+        return launch_trmm_f32(static_cast<const float*>(l), ldl, static_cast<const float*>(b), ldb,
+                               static_cast<float*>(c), ldc, n, m, s);
     }
     return hipGetLastError();
 }
@@ -1246,21 +835,9 @@ hipError_t launch_linear(int dtype, const void* x, int ldx, const void* w, const
         if (act == 2) return launch_bf16_act<2>(x, ldx, w, bias, residual, ldr, y, ldy, T, K, N, plan, s);
         return launch_bf16_act<0>(x, ldx, w, bias, residual, ldr, y, ldy, T, K, N, plan, s);
     }
-    const dim3 grid((T + 63) / 64, (N + 63) / 64);
-    const float* xf = static_cast<const float*>(x);
-    const float* wf = static_cast<const float*>(w);
-    const float* bf = static_cast<const float*>(bias);
-    const float* rf = static_cast<const float*>(residual);
-    float* yf = static_cast<float*>(y);
-    if (f32_mfma_ok(x, ldx, w, bias, residual, ldr, y, ldy, K, N)) {
-        if (act == 1) return launch_f32_mfma_act<1>(xf, ldx, wf, bf, rf, ldr, yf, ldy, T, K, N, s);
-        if (act == 2) return launch_f32_mfma_act<2>(xf, ldx, wf, bf, rf, ldr, yf, ldy, T, K, N, s);
-        return launch_f32_mfma_act<0>(xf, ldx, wf, bf, rf, ldr, yf, ldy, T, K, N, s);
-    }
-    if (act == 1) hipLaunchKernelGGL(k_gemm_f32<1>, grid, dim3(256), 0, s, xf, ldx, wf, bf, rf, ldr, yf, ldy, T, K, N);
-    else if (act == 2) hipLaunchKernelGGL(k_gemm_f32<2>, grid, dim3(256), 0, s, xf, ldx, wf, bf, rf, ldr, yf, ldy, T, K, N);
-    else hipLaunchKernelGGL(k_gemm_f32<0>, grid, dim3(256), 0, s, xf, ldx, wf, bf, rf, ldr, yf, ldy, T, K, N);
-    return hipGetLastError();
+    return launch_linear_f32(static_cast<const float*>(x), ldx, static_cast<const float*>(w),
+                             static_cast<const float*>(bias), static_cast<const float*>(residual), ldr, act,
+                             static_cast<float*>(y), ldy, T, K, N, s);
 }
 
 }  // namespace rag
