@@ -128,6 +128,23 @@ __device__ __forceinline__ bool vgemm_ok(const VgemmArgs& va, bool bf16) {
     return true;
 }
 
+// One bf16 packed linear call.
+struct LinearArgs {
+    const uint16_t* x;
+    int ldx;
+    const uint16_t* w;
+    const uint16_t* bias;
+    const uint16_t* residual;
+    int ldr;
+    uint16_t* y;
+    int ldy, T, K, N;
+};
+
+// Smaller tiles for small launches (gemm_small.hip): the tile form to run (1 .. 4), or 0
+// where the 128 x 256 tiles are estimated faster; and its launch.
+int small_gemm_choice(int64_t T, int64_t K, int64_t N, int64_t cus);
+hipError_t launch_gemm_small(int which, int act, const LinearArgs& a, const PlanView* plan, hipStream_t s);
+
 // fp32 launchers (gemm_f32.hip), called by the launchers that take both types.
 hipError_t launch_linear_f32(const float* x, int ldx, const float* w, const float* bias, const float* residual, int ldr,
                              int act, float* y, int ldy, int T, int K, int N, hipStream_t s);
