@@ -4,8 +4,8 @@
 //                   block), walking every 64-key tile of its rows; fp32: one
 //                   item = one 64x64 score tile.  No tile crosses a sequence
 //                   boundary, so no padded work is done beyond predicated edges
-//   ragged softmax  one wave per token: the token's H rows (each L_b scores)
-//                   are contiguous in the X[b][i][h][j] layout
+//   ragged softmax  one wave per token (or group of its heads): the token's H rows
+//                   (each L_b scores) are contiguous in the X[b][i][h][j] layout
 //   ragged Attn.V   one workgroup item = 64 query rows of one sequence and head,
 //                   reducing over that sequence's L_b keys
 //   fused           one (sequence, head, 64-query tile) item per two-wave
@@ -331,91 +331,114 @@ __global__ __launch_bounds__(256) void k_qkt_f32(PlanArgs pa, const float* __res
 // Softmax
 // ---------------------------------------------------------------------------
 
+// One 16-byte chunk of a score row: kPer values in fp32.  A row starts at any element, so
+// the vectors are declared with the element's alignment (global memory takes vector
+// accesses at any byte on this target).
 template <bool BF16>
-struct Elem;
+struct RowIO;
 template <>
-struct Elem<true> {
+struct RowIO<true> {
     using T = uint16_t;
-    static __device__ __forceinline__ float load(const T* p) { return bf16_to_f32(*p); }
-    static __device__ __forceinline__ void store(T* p, float v) { *p = f32_to_bf16(v); }
+    typedef uint32_t Vec __attribute__((ext_vector_type(4), aligned(2)));
+    static constexpr int kPer = 8;
+    static __device__ __forceinline__ float load1(const T* p) { return bf16_to_f32(*p); }
+    static __device__ __forceinline__ void store1(T* p, float v) { *p = f32_to_bf16(v); }
     static __device__ __forceinline__ float exp(float x) { return __expf(x); }
-};
-template <>
-struct Elem<false> {
-    using T = float;
-    static __device__ __forceinline__ float load(const T* p) { return *p; }
-    static __device__ __forceinline__ void store(T* p, float v) { *p = v; }
-    static __device__ __forceinline__ float exp(float x) { return expf(x); }
-};
-
-constexpr int kSoftmaxRegs = 8;  // rows up to 64 * 8 = 512 scores stay in registers
-
-// One bf16 score row of n values starting at element E (any alignment) with R
-// aligned 16-byte chunks per lane (n + 7 <= 512 R): loads through the
-// range-checked descriptor rs (based at element e_base, a multiple of 8), an
-// exact max and sum over the row, whole chunks stored with 16-byte stores and
-// the partial chunks at both ends element by element (their other elements
-// belong to the neighbouring rows, so a whole-chunk store could race with them).
-template <int R>
-__device__ __forceinline__ void softmax_row_chunks(__amdgpu_buffer_rsrc_t rs, int64_t e_base, int64_t E, int n,
-                                                   uint16_t* P, int lane) {
-    const int64_t c0 = E >> 3;        // first chunk of the row
-    const int sh = (int)(E & 7);      // the row's first element within it
-    const int nch = (sh + n + 7) >> 3;
-    float x[R][8];
-    float m = -FLT_MAX;
+    static __device__ __forceinline__ void unpack(const Vec& w, float* v) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int c = lane + kWave * r;
-        u32x4 raw = {0u, 0u, 0u, 0u};
-        if (c < nch)
-            raw = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)((c0 + c) * 8 - e_base) * 2, 0, 0));
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int j = 8 * c + e - sh;
-            const uint32_t w = raw[e >> 1];
-            const float v = __uint_as_float((e & 1) ? (w & 0xffff0000u) : (w << 16));
-            x[r][e] = (j >= 0 && j < n) ? v : -FLT_MAX;
-            m = fmaxf(m, x[r][e]);
+        for (int e = 0; e < 4; ++e) {
+            v[2 * e] = lo_bf16(w[e]);
+            v[2 * e + 1] = hi_bf16(w[e]);
         }
     }
-    m = wave_max(m);
-    float sum = 0.f;
+    static __device__ __forceinline__ Vec pack(const float* v, float f) {
+        return Vec{pack_bf16x2(v[0] * f, v[1] * f), pack_bf16x2(v[2] * f, v[3] * f), pack_bf16x2(v[4] * f, v[5] * f),
+                   pack_bf16x2(v[6] * f, v[7] * f)};
+    }
+};
+template <>
+struct RowIO<false> {
+    using T = float;
+    typedef float Vec __attribute__((ext_vector_type(4), aligned(4)));
+    static constexpr int kPer = 4;
+    static __device__ __forceinline__ float load1(const T* p) { return *p; }
+    static __device__ __forceinline__ void store1(T* p, float v) { *p = v; }
+    static __device__ __forceinline__ float exp(float x) { return expf(x); }
+    static __device__ __forceinline__ void unpack(const Vec& w, float* v) {
 #pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int j = 8 * (lane + kWave * r) + e - sh;
-            x[r][e] = (j >= 0 && j < n) ? __expf(x[r][e] - m) : 0.f;
-            sum += x[r][e];
-        }
-    const float inv = 1.0f / wave_sum(sum);
+        for (int e = 0; e < 4; ++e) v[e] = w[e];
+    }
+    static __device__ __forceinline__ Vec pack(const float* v, float f) {
+        return Vec{v[0] * f, v[1] * f, v[2] * f, v[3] * f};
+    }
+};
+
+// The rows of heads [h0, h1) of one token: n values each, ld apart, the first row at
+// element `row0`.  LR lanes per row (64 / LR rows at once), R chunks per lane: n <= LR *
+// R * kPer, n >= kPer.  A row's last chunk is moved back so that it ends with the row: its
+// first values are then held twice, counted once in the sum and stored twice with the
+// same value, and no partial chunk exists.  (Chunks at aligned addresses instead left
+// both ends of every row to element stores, eight instructions per row.)
+template <bool BF16, int LR, int R>
+__device__ __forceinline__ void softmax_rows(const typename RowIO<BF16>::T* S, typename RowIO<BF16>::T* P, int64_t row0,
+                                             int ld, int n, int h0, int h1, int lane) {
+    using IO = RowIO<BF16>;
+    using Vec = typename IO::Vec;
+    constexpr int E = IO::kPer;
+    const int sub = lane % LR, rr = lane / LR;
+    int j0[R], skip[R];  // a chunk's first element; how many of its values an earlier chunk holds
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int c = lane + kWave * r;
-        if (c >= nch) continue;
-        const int j0 = 8 * c - sh;  // row position of the chunk's first element
-        uint16_t* dst = P + (c0 + c) * 8;
-        if (j0 >= 0 && j0 + 8 <= n) {
-            u32x4 o;
+        const int j = E * (sub + LR * r);
+        j0[r] = min(j, n - E);
+        skip[r] = j - j0[r];  // >= E: a lane past the row's end
+    }
+    Vec next[R];
+    auto load = [&](int h) {
+        const int64_t base = row0 + (int64_t)min(h + rr, h1 - 1) * ld;
 #pragma unroll
-            for (int d = 0; d < 4; ++d) o[d] = pack_bf16x2(x[r][2 * d] * inv, x[r][2 * d + 1] * inv);
-            *reinterpret_cast<u32x4*>(dst) = o;
-        } else {
+        for (int r = 0; r < R; ++r) next[r] = *reinterpret_cast<const Vec*>(S + base + j0[r]);
+    };
+    load(h0);
+    for (int h = h0; h < h1; h += kWave / LR) {
+        float x[R][E];
+        float m = -FLT_MAX;
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (j0 + e >= 0 && j0 + e < n) dst[e] = f32_to_bf16(x[r][e] * inv);
+        for (int r = 0; r < R; ++r) {
+            IO::unpack(next[r], x[r]);
+#pragma unroll
+            for (int e = 0; e < E; ++e) m = fmaxf(m, x[r][e]);
+        }
+        if (h + kWave / LR < h1) load(h + kWave / LR);
+        m = group_max<LR>(m);
+        float sum = 0.f;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                x[r][e] = IO::exp(x[r][e] - m);
+                sum += e >= skip[r] ? x[r][e] : 0.f;
+            }
+        const float inv = 1.0f / group_sum<LR>(sum);
+        if (h + rr < h1) {
+            const int64_t base = row0 + (int64_t)(h + rr) * ld;
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (skip[r] < E) *reinterpret_cast<Vec*>(P + base + j0[r]) = IO::pack(x[r], inv);
         }
     }
 }
 
+// One wave per token and group of `hg` heads (blockIdx.y): a wave's rows are a chain of
+// loads and reductions, so small batches split a token's heads over waves.
 template <bool BF16>
-__global__ __launch_bounds__(256) void k_softmax(PlanArgs pa, const typename Elem<BF16>::T* S,
-                                                  typename Elem<BF16>::T* P, int64_t score_cap, int T, int causal) {
-    using E = Elem<BF16>;
+__global__ __launch_bounds__(256) void k_softmax(PlanArgs pa, const typename RowIO<BF16>::T* S,
+                                                  typename RowIO<BF16>::T* P, int64_t score_cap, int T, int causal,
+                                                  int hg) {
+    using IO = RowIO<BF16>;
     if (!plan_ok(pa, score_cap)) return;
-    // wave-uniform by construction; made explicit so that the token's offsets and
-    // the score rows' buffer descriptor stay in scalar registers
+    // wave-uniform by construction; made explicit so that the token's offsets stay in
+    // scalar registers
     const int wave = uni(threadIdx.x / kWave), lane = threadIdx.x % kWave;
     const int t = blockIdx.x * 4 + wave;
     if (t >= T) return;
@@ -425,72 +448,44 @@ __global__ __launch_bounds__(256) void k_softmax(PlanArgs pa, const typename Ele
     const int pos = t - pa.tok_off[b];
     const int L = causal ? pos + 1 : ld;          // scores in each of this token's rows
     const int64_t row0 = pa.att_off[b] + (int64_t)pos * H * ld;
-    if (L <= kWave) {
-        // 64/G rows per pass, G = next power of two >= L lanes per row
-        int G = 1;
-        while (G < L) G <<= 1;
-        const int R = kWave / G, r = lane / G, e = lane % G;
-        for (int h0 = 0; h0 < H; h0 += R) {
-            const int h = h0 + r;
-            const bool valid = (h < H) && (e < L);
+    const int h0 = blockIdx.y * hg, h1 = min(H, h0 + hg);
+    constexpr int E = IO::kPer;
+    if (L < E) {
+        // eight lanes per row, one value each
+        const int e = lane % 8;
+        for (int h = h0 + lane / 8; h - lane / 8 < h1; h += kWave / 8) {
+            const bool valid = h < h1 && e < L;
             const int64_t off = row0 + (int64_t)h * ld + e;
-            const float x = valid ? E::load(S + off) : -FLT_MAX;
-            const float m = group_max(x, G);
-            const float ex = valid ? E::exp(x - m) : 0.f;
-            const float s = group_sum(ex, G);
-            if (valid) E::store(P + off, ex * (1.0f / s));
+            const float x = valid ? IO::load1(S + off) : -FLT_MAX;
+            const float m = group_max<8>(x);  // (all lanes take part)
+            const float ex = valid ? IO::exp(x - m) : 0.f;
+            const float inv = 1.0f / group_sum<8>(ex);
+            if (valid) IO::store1(P + off, ex * inv);
         }
-    } else if (BF16 && L + 7 <= 8 * kWave * 2) {
-        // aligned 16-byte chunks: the token's rows are one span of H * ld scores
-        const int64_t e_base = row0 & ~(int64_t)7;
-        const int64_t span_end = min(score_cap, row0 + (int64_t)(H - 1) * ld + L);
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<void*>(static_cast<const void*>(S + e_base)), 0,
-            (uint32_t)min<int64_t>(((span_end - e_base) * 2 + 3) & ~(int64_t)3, (int64_t)0x7ffffffc), 0x00020000);
-        uint16_t* const Pb = reinterpret_cast<uint16_t*>(P);
-        if (L + 7 <= 8 * kWave) {
-            for (int h = 0; h < H; ++h) softmax_row_chunks<1>(rs, e_base, row0 + (int64_t)h * ld, L, Pb, lane);
-        } else {
-            for (int h = 0; h < H; ++h) softmax_row_chunks<2>(rs, e_base, row0 + (int64_t)h * ld, L, Pb, lane);
-        }
-    } else if (L <= kWave * kSoftmaxRegs) {
-        for (int h = 0; h < H; ++h) {
-            const int64_t rp = row0 + (int64_t)h * ld;
-            float x[kSoftmaxRegs];
-            float m = -FLT_MAX;
-#pragma unroll
-            for (int u = 0; u < kSoftmaxRegs; ++u) {
-                const int j = lane + kWave * u;
-                x[u] = j < L ? E::load(S + rp + j) : -FLT_MAX;
-                m = fmaxf(m, x[u]);
-            }
-            m = wave_max(m);
-            float s = 0.f;
-#pragma unroll
-            for (int u = 0; u < kSoftmaxRegs; ++u) {
-                const int j = lane + kWave * u;
-                x[u] = j < L ? E::exp(x[u] - m) : 0.f;
-                s += x[u];
-            }
-            const float inv = 1.0f / wave_sum(s);
-#pragma unroll
-            for (int u = 0; u < kSoftmaxRegs; ++u) {
-                const int j = lane + kWave * u;
-                if (j < L) E::store(P + rp + j, x[u] * inv);
-            }
-        }
+    } else if (L <= 8 * E) {
+        softmax_rows<BF16, 8, 1>(S, P, row0, ld, L, h0, h1, lane);
+    } else if (L <= 16 * E) {
+        softmax_rows<BF16, 16, 1>(S, P, row0, ld, L, h0, h1, lane);
+    } else if (L <= 32 * E) {
+        softmax_rows<BF16, 32, 1>(S, P, row0, ld, L, h0, h1, lane);
+    } else if (L <= 64 * E) {
+        softmax_rows<BF16, 64, 1>(S, P, row0, ld, L, h0, h1, lane);
+    } else if (L <= 128 * E) {
+        softmax_rows<BF16, 64, 2>(S, P, row0, ld, L, h0, h1, lane);
+    } else if (!BF16 && L <= 256 * E) {
+        softmax_rows<BF16, 64, BF16 ? 2 : 4>(S, P, row0, ld, L, h0, h1, lane);
     } else {
         // long rows: max pass, sum pass, write pass (each element is read before
         // the same lane overwrites it, so in-place use is safe)
-        for (int h = 0; h < H; ++h) {
+        for (int h = h0; h < h1; ++h) {
             const int64_t rp = row0 + (int64_t)h * ld;
             float m = -FLT_MAX;
-            for (int j = lane; j < L; j += kWave) m = fmaxf(m, E::load(S + rp + j));
+            for (int j = lane; j < L; j += kWave) m = fmaxf(m, IO::load1(S + rp + j));
             m = wave_max(m);
             float s = 0.f;
-            for (int j = lane; j < L; j += kWave) s += E::exp(E::load(S + rp + j) - m);
+            for (int j = lane; j < L; j += kWave) s += IO::exp(IO::load1(S + rp + j) - m);
             const float inv = 1.0f / wave_sum(s);
-            for (int j = lane; j < L; j += kWave) E::store(P + rp + j, E::exp(E::load(S + rp + j) - m) * inv);
+            for (int j = lane; j < L; j += kWave) IO::store1(P + rp + j, IO::exp(IO::load1(S + rp + j) - m) * inv);
         }
     }
 }
@@ -1074,13 +1069,20 @@ hipError_t launch_softmax(const PlanView& p, int dtype, const void* scores, void
                           bool causal, hipStream_t s) {
     if (p.total_tokens == 0) return hipSuccess;
     const PlanArgs pa = plan_args(p);
-    const int grid = (p.total_tokens + 3) / 4;
+    // heads per wave: two waves per wave slot (32 per CU) as far as the heads go.  1 to 8
+    // per slot measured alike at T = 8879 and 35475; at T = 2236, where one wave per
+    // token fills a quarter of the slots, splitting took fp32 12.1 -> 7.2 us together
+    // with the in-register reductions
+    const int64_t want = (int64_t)device_cu_count() * 64;
+    const int parts = (int)std::min<int64_t>(p.heads, std::max<int64_t>(1, want / p.total_tokens));
+    const int hg = (p.heads + parts - 1) / parts;
+    const dim3 grid((p.total_tokens + 3) / 4, (p.heads + hg - 1) / hg);
     if (dtype == 1)
-        hipLaunchKernelGGL(k_softmax<true>, dim3(grid), dim3(256), 0, s, pa, static_cast<const uint16_t*>(scores),
-                           static_cast<uint16_t*>(probs), score_cap, p.total_tokens, int(causal));
+        hipLaunchKernelGGL(k_softmax<true>, grid, dim3(256), 0, s, pa, static_cast<const uint16_t*>(scores),
+                           static_cast<uint16_t*>(probs), score_cap, p.total_tokens, int(causal), hg);
     else
-        hipLaunchKernelGGL(k_softmax<false>, dim3(grid), dim3(256), 0, s, pa, static_cast<const float*>(scores),
-                           static_cast<float*>(probs), score_cap, p.total_tokens, int(causal));
+        hipLaunchKernelGGL(k_softmax<false>, grid, dim3(256), 0, s, pa, static_cast<const float*>(scores),
+                           static_cast<float*>(probs), score_cap, p.total_tokens, int(causal), hg);
     return hipGetLastError();
 }
 

@@ -44,28 +44,44 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 __device__ __forceinline__ float lo_bf16(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float hi_bf16(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
+// All-reduce within aligned groups of G lanes (a power of two), by moves inside the
+// vector unit: quad permutes and mirrors inside a row of 16 lanes, then lane swaps
+// between rows and between the half waves.  (Shuffles go through the LDS unit, about
+// 100 cycles each: a row softmax's 12 in a chain were most of its time.)
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float v) {
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), CTRL, 0xf, 0xf, true));
+}
+
+template <int G, typename Op>
+__device__ __forceinline__ float group_reduce(float v, Op op) {
+    static_assert(G == 1 || G == 2 || G == 4 || G == 8 || G == 16 || G == 32 || G == 64, "group size");
+    if constexpr (G >= 2) v = op(v, dpp_move<0xb1>(v));    // quad_perm 1, 0, 3, 2
+    if constexpr (G >= 4) v = op(v, dpp_move<0x4e>(v));    // quad_perm 2, 3, 0, 1
+    if constexpr (G >= 8) v = op(v, dpp_move<0x141>(v));   // half-row mirror: the other quad of 8
+    if constexpr (G >= 16) v = op(v, dpp_move<0x140>(v));  // row mirror: the other 8 of 16
+    if constexpr (G >= 32) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    }
+    if constexpr (G >= 64) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    }
     return v;
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
+template <int G>
+__device__ __forceinline__ float group_max(float v) {
+    return group_reduce<G>(v, [](float a, float b) { return fmaxf(a, b); });
+}
+template <int G>
+__device__ __forceinline__ float group_sum(float v) {
+    return group_reduce<G>(v, [](float a, float b) { return a + b; });
 }
 
-// Reductions within aligned groups of `g` lanes (g a power of two <= 64).
-__device__ __forceinline__ float group_max(float v, int g) {
-    for (int o = g >> 1; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-    return v;
-}
-
-__device__ __forceinline__ float group_sum(float v, int g) {
-    for (int o = g >> 1; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
-}
+__device__ __forceinline__ float wave_max(float v) { return group_max<kWave>(v); }
+__device__ __forceinline__ float wave_sum(float v) { return group_sum<kWave>(v); }
 
 __device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
 
