@@ -32,15 +32,12 @@ struct PlanArgs {
     const int32_t* tok_seq;
     const int32_t* qkt_items;
     const int32_t* av_items;
-    const int32_t* order;
-    const int32_t* av_item_off;
     int32_t* status;
     int batch, heads;
 };
 
 PlanArgs plan_args(const PlanView& p) {
-    return PlanArgs{p.lengths, p.tok_off, p.att_off, p.tok_seq, p.qkt_items, p.av_items, p.order, p.av_item_off,
-                    p.status, p.batch, p.heads};
+    return PlanArgs{p.lengths, p.tok_off, p.att_off, p.tok_seq, p.qkt_items, p.av_items, p.status, p.batch, p.heads};
 }
 
 // True if the plan is valid and the score buffer large enough; otherwise one
@@ -88,26 +85,32 @@ __device__ __forceinline__ int kv_off(int row, int col) { return row * kHeadDim 
 // when G = H), so a workgroup reads or writes whole cache lines, and the item
 // reads each of its heads' K (or V) panels of the sequence once.  Items follow
 // the plan's Attn.V list (sequences longest first, then head groups, then query
-// blocks); a workgroup finds its item's sequence by a wave-wide search of the
-// per-sequence item prefix, and consecutive items (the query blocks of one head
+// blocks), and consecutive items (the query blocks of one head
 // group) go to one XCD in runs, so they share its K / V panels in that L2.
 constexpr int kOpRun = 8;  // consecutive items per XCD
 
-// Largest k with off[k] / G <= g: the sorted sequence holding item g (off holds
-// H entries per 64-query block of each sequence, so off[k] / G counts the items
-// of G heads each, G a divisor of H).
-__device__ __forceinline__ int item_sequence(const int32_t* off, int B, int G, int g) {
-    const int lane = threadIdx.x % kWave;
-    int lo = 0, span = B;
-    while (span > 1) {
-        const int st = (span + kWave - 1) / kWave;
-        const bool le = lane * st < span && off[lo + lane * st] / G <= g;
-        const uint64_t m = __ballot(le);  // lane 0 always holds (off[lo] / G <= g)
-        const int last = 63 - __builtin_clzll(m);
-        lo += last * st;
-        span = min(st, span - last * st);
-    }
-    return lo;
+// Item g of the items of G heads each: entry g * G of the plan's Attn.V list belongs to
+// its sequence (a sequence's entries, H per query block, start at a multiple of G), and
+// that entry's position h * nb + ti within the sequence, over G, is the item's.  Two
+// dependent loads (a search of the per-sequence prefix took four).
+struct OpItem {
+    int b, L, t0, ti, h0;  // sequence, its length and first token; query block; first head
+    int64_t base;          // the sequence's first score
+};
+
+__device__ __forceinline__ OpItem op_item_at(const PlanArgs& pa, int G, int g) {
+    const int32_t* const e = pa.av_items + 3 * (int64_t)g * G;
+    OpItem it;
+    it.b = uni(e[0]);
+    const int eh = uni(e[1]), eti = uni(e[2]);
+    it.L = uni(pa.lengths[it.b]);
+    it.t0 = uni(pa.tok_off[it.b]);
+    it.base = uni64(pa.att_off[it.b]);
+    const int nb = (it.L + kTile - 1) / kTile;  // query blocks of the sequence
+    const int local = (eh * nb + eti) / G, hg = local / nb;
+    it.ti = local - hg * nb;
+    it.h0 = hg * G;
+    return it;
 }
 
 __device__ __forceinline__ int op_item(int bid, int grid) {  // grid: a multiple of 8 * kOpRun
@@ -123,7 +126,7 @@ __device__ __forceinline__ int op_item(int bid, int grid) {  // grid: a multiple
 // any element, so a chunk is cut from two LDS chunks by a funnel shift), and
 // 2-byte stores for the partial chunks at both ends of each row piece.
 constexpr int kPiece = 4 * kTile;         // keys per written row piece: one tile per wave
-constexpr int kPieceRow = kPiece + 4;     // LDS row (elements): room for the shifted read
+constexpr int kPieceRow = kPiece + 8;     // LDS row (elements): 16-byte aligned, rows four banks apart
 constexpr int kQkWaves = 8, kQkThreads = kQkWaves * kWave;
 constexpr int kQkKeys = kPiece / kQkWaves;  // keys of a piece per wave
 constexpr int kQkJb = kQkKeys / 16;         // 16-key MFMA blocks per wave
@@ -141,14 +144,9 @@ __global__ __launch_bounds__(kQkThreads) void k_qkt_bf16(PlanArgs pa, const uint
     for (int base_it = 0; base_it < n_items; base_it += gridDim.x) {
         const int g = base_it + op_item(blockIdx.x, gridDim.x);
         if (g >= n_items) break;
-        const int kk = uni(item_sequence(pa.av_item_off, pa.batch, G, g));
-        const int b = uni(pa.order[kk]);
-        const int local = g - uni(pa.av_item_off[kk]) / G;
-        const int nb = (uni(pa.lengths[b]) + kTile - 1) / kTile;  // query blocks of the sequence
-        const int hg = local / nb, ti = local - hg * nb, h0 = hg * G;  // heads h0 .. h0 + G - 1
-        const int L = uni(pa.lengths[b]);
-        const int t0 = uni(pa.tok_off[b]);
-        const int64_t base = uni64(pa.att_off[b]);
+        const OpItem item = op_item_at(pa, G, g);  // heads h0 .. h0 + G - 1
+        const int L = item.L, t0 = item.t0, ti = item.ti, h0 = item.h0;
+        const int64_t base = item.base;
         const int i0 = ti * kTile;                // the block's first query row
         const int rows = min(kTile, L - i0);
         // keys the block needs: all, or (masked) up to its last row
@@ -222,44 +220,28 @@ __global__ __launch_bounds__(kQkThreads) void k_qkt_bf16(PlanArgs pa, const uint
                                   pack_bf16x2(acc[jb][rg][2] * scale, acc[jb][rg][3] * scale)};
             }
             __syncthreads();
-            // Row r (threads 8 r .. 8 r + 7) holds keys p0 .. p0 + n - 1 at elements G0 ..
-            // G0 + n - 1 of S.  Its whole 16-byte chunks fa .. fb - 1 start at local key
-            // sh + 8 (c - fa), sh = 8 fa - G0 the same for every chunk of the row: five
-            // dwords read from LDS at dword 4 (c - fa) + sh / 2, funneled by 2 (sh & 1)
-            // bytes, give the chunk.  The partial chunks at both ends (under 8 elements
-            // each) are 2-byte stores, one per thread and end.
+            // Row r holds keys p0 .. p0 + n - 1: 32 threads store it as 16-byte chunks at the
+            // row's element offset (any alignment), two rows of 512 bytes per wave
+            // instruction; the up to seven elements past the last whole chunk follow one per
+            // thread.  The LDS reads are ones the compiler does not see, so it adds no wait
+            // for the Q copy that may be in flight (it cannot tell the buffers apart).
             {
-                const int r = threadIdx.x >> 3, sub = threadIdx.x & 7;
-                const int n = causal ? min(pn, i0 + r + 1 - p0) : pn;
-                if (r < rows && n > 0) {
-                    const int64_t G0 = base + ((int64_t)(i0 + r) * H + h) * L + p0;
-                    const int64_t fa = (G0 + 7) >> 3, fb = (G0 + n) >> 3;
-                    const int sh = (int)(8 * fa - G0);  // 0 .. 7
-                    const int nch = (int)(fb - fa);     // may be negative for a short row
-                    const uint32_t* const src = reinterpret_cast<const uint32_t*>(&st[r][0]) + (sh >> 1);
-                    const uint32_t rb = (sh & 1) * 2;
-                    uint16_t* const dst = S + 8 * fa;
-                    for (int cc = sub; cc < nch; cc += 8) {
-                        // the five dwords by LDS reads the compiler does not see, so it adds
-                        // no wait for the Q copy that may be in flight (it cannot tell the
-                        // buffers apart)
-                        const uint32_t da = (uint32_t)(uintptr_t)(src + 4 * cc);
-                        u32x2 d01, d23;
-                        uint32_t d4;
-                        asm volatile(
-                            "ds_read2_b32 %0, %3 offset1:1\n\tds_read2_b32 %1, %3 offset0:2 offset1:3\n\t"
-                            "ds_read_b32 %2, %3 offset:16\n\ts_waitcnt lgkmcnt(0)"
-                            : "=&v"(d01), "=&v"(d23), "=&v"(d4)
-                            : "v"(da)
-                            : "memory");
-                        const uint32_t d0 = d01[0], d1 = d01[1], d2 = d23[0], d3 = d23[1];
-                        *reinterpret_cast<u32x4*>(dst + 8 * cc) =
-                            u32x4{__builtin_amdgcn_alignbyte(d1, d0, rb), __builtin_amdgcn_alignbyte(d2, d1, rb),
-                                  __builtin_amdgcn_alignbyte(d3, d2, rb), __builtin_amdgcn_alignbyte(d4, d3, rb)};
+                typedef uint32_t Chunk __attribute__((ext_vector_type(4), aligned(2)));
+                const int c = threadIdx.x % 32;
+#pragma unroll
+                for (int rr = 0; rr < kTile / (kQkThreads / 32); ++rr) {
+                    const int r = rr * (kQkThreads / 32) + threadIdx.x / 32;
+                    const int n = r < rows ? (causal ? min(pn, i0 + r + 1 - p0) : pn) : 0;
+                    uint16_t* const dst = S + base + ((int64_t)(i0 + r) * H + h) * L + p0;
+                    if (8 * c + 8 <= n) {
+                        u32x4 v;
+                        asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)"
+                                     : "=&v"(v)
+                                     : "v"((uint32_t)(uintptr_t)&st[r][8 * c])
+                                     : "memory");
+                        *reinterpret_cast<Chunk*>(dst + 8 * c) = v;
                     }
-                    const int head = min(sh, n), tail0 = max((int)(8 * fb - G0), head);
-                    if (sub < head) S[G0 + sub] = st[r][sub];
-                    if (tail0 + sub < n) S[G0 + tail0 + sub] = st[r][tail0 + sub];
+                    if (n > 0 && c < (n & 7)) dst[(n & ~7) + c] = st[r][(n & ~7) + c];
                 }
             }
             if (f + 1 < F) {
@@ -537,14 +519,9 @@ __global__ __launch_bounds__(256) void k_attn_v_bf16(PlanArgs pa, const uint16_t
     for (int base_it = 0; base_it < n_items; base_it += gridDim.x) {
         const int g = base_it + op_item(blockIdx.x, gridDim.x);
         if (g >= n_items) break;  // uniform over the workgroup
-        const int kk = uni(item_sequence(pa.av_item_off, pa.batch, G, g));
-        const int b = uni(pa.order[kk]);
-        const int local = g - uni(pa.av_item_off[kk]) / G;
-        const int nb = (uni(pa.lengths[b]) + kTile - 1) / kTile;  // query blocks of the sequence
-        const int hg = local / nb, ti = local - hg * nb, h0 = hg * G;  // heads h0 .. h0 + G - 1
-        const int L = uni(pa.lengths[b]);
-        const int t0 = uni(pa.tok_off[b]);
-        const int64_t base = uni64(pa.att_off[b]);
+        const OpItem item = op_item_at(pa, G, g);  // heads h0 .. h0 + G - 1
+        const int L = item.L, t0 = item.t0, ti = item.ti, h0 = item.h0;
+        const int64_t base = item.base;
         const int rows = min(kTile, L - ti * kTile);
         const int i = ti * kTile + wave * 16 + l16;  // this lane's query row (valid if < ti*64 + rows)
         const bool row_ok = wave * 16 + l16 < rows;
