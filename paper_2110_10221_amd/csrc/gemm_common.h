@@ -66,6 +66,13 @@ __device__ __forceinline__ bool trmm_tile_coords(int bid, int tiles_m, int tiles
     return true;
 }
 
+// List position of a workgroup when runs of `run` consecutive positions go to one XCD, the
+// runs round-robin; a permutation of [0, grid) when the grid is a multiple of 8 * run.
+__device__ __forceinline__ int dealt_to_xcds(int bid, int run) {
+    const int xcd = bid % 8, idx = bid / 8;
+    return ((idx / run) * 8 + xcd) * run + idx % run;
+}
+
 // Workgroup-uniform values made so explicitly: the compiler cannot keep plan reads
 // in scalar registers where the same kernel may write the status word (atomicOr),
 // and a buffer descriptor built from a per-lane value becomes a per-lane loop.

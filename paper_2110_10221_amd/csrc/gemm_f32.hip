@@ -303,7 +303,7 @@ using F32Tiny = F32Cfg<32, 32, 1, 1, 4, 4>;
 // last, partial round (n_full on) run as four quarters each, one per workgroup, of CS
 // (half of C's sides), so that round takes about a quarter of a tile's time.
 template <class C, class CS, int ACT, bool WIDE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void k_gemm_f32(const float* __restrict__ x, int ldx, const float* __restrict__ w, const float* __restrict__ bias,
                 const float* residual, int ldr, float* y, int ldy, int T, int K, int N, int tiles_m, int tiles_n,
                 int n_full) {
@@ -432,19 +432,19 @@ hipError_t launch_linear_act(const float* x, int ldx, const float* w, const floa
 
 // ---------------------------------------------------------------------------
 // Variable-sized batched GEMM: one workgroup per C-sized part of a list entry's
-// 128 x 256 tile; parts past the problem's edge exit at once.  Parts are dealt to the
-// XCDs in runs of kVgemmRun consecutive entries' parts (see the bf16 kernel).
+// 128 x 256 tile; parts past the problem's edge exit at once.  Runs of `run` consecutive
+// entries go to one XCD (they mostly come from one problem and share its operand panels
+// in that L2), the runs round-robin.  Long runs leave some XCDs a run short at the end:
+// about 50 runs per XCD measured best (batch 32 of sizes 65..1023, 400 entries: 139 us
+// at one entry per run, 154 at 4, 162 at 16; sizes 512..1408, 900 entries: 475 at 2, 504 at 16).
 // ---------------------------------------------------------------------------
-constexpr int kVgemmRun = 16;
-
 template <class C>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void k_vgemm_f32(VgemmArgs va, const float* __restrict__ a, const float* __restrict__ b, float* c) {
-    constexpr int kPm = kVgemmTileM / C::TM, kParts = kPm * (kVgemmTileN / C::TN), kRun = kVgemmRun * kParts;
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
+void k_vgemm_f32(VgemmArgs va, const float* __restrict__ a, const float* __restrict__ b, float* c, int run) {
+    constexpr int kPm = kVgemmTileM / C::TM, kParts = kPm * (kVgemmTileN / C::TN);
     extern __shared__ __attribute__((aligned(16))) float fsm[];
     if (!vgemm_ok(va, false)) return;
-    const int xcd = blockIdx.x % 8, idx = blockIdx.x / 8;
-    const int part = ((idx / kRun) * 8 + xcd) * kRun + idx % kRun, e = part / kParts, sub = part % kParts;
+    const int part = dealt_to_xcds(blockIdx.x, run * kParts), e = part / kParts, sub = part % kParts;
     if (e >= uni(va.status[1])) return;
     const VgemmTile t = vgemm_tile(va, e);
     const int m0 = t.m0 + sub % kPm * C::TM, n0 = t.n0 + sub / kPm * C::TN;
@@ -462,7 +462,9 @@ void k_vgemm_f32(VgemmArgs va, const float* __restrict__ a, const float* __restr
 template <class C>
 hipError_t launch_vgemm_tiles(const VgemmArgs& va, int64_t tile_cap, const float* a, const float* b, float* c,
                               hipStream_t s) {
-    constexpr int64_t kParts = (kVgemmTileM / C::TM) * (kVgemmTileN / C::TN), kQuantum = 8 * kVgemmRun * kParts;
+    constexpr int64_t kParts = (kVgemmTileM / C::TM) * (kVgemmTileN / C::TN);
+    const int run = (int)std::min<int64_t>(16, std::max<int64_t>(1, tile_cap / 400));
+    const int64_t quantum = 8 * run * kParts;
     static bool attr_set = false;  // benign race: every thread sets the same value
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_vgemm_f32<C>),
@@ -470,8 +472,8 @@ hipError_t launch_vgemm_tiles(const VgemmArgs& va, int64_t tile_cap, const float
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    const int64_t grid = (tile_cap * kParts + kQuantum - 1) / kQuantum * kQuantum;
-    hipLaunchKernelGGL(k_vgemm_f32<C>, dim3((unsigned)grid), dim3(256), C::kLdsBytes, s, va, a, b, c);
+    const int64_t grid = (tile_cap * kParts + quantum - 1) / quantum * quantum;
+    hipLaunchKernelGGL(k_vgemm_f32<C>, dim3((unsigned)grid), dim3(256), C::kLdsBytes, s, va, a, b, c, run);
     return hipGetLastError();
 }
 
@@ -479,8 +481,11 @@ hipError_t launch_vgemm_tiles(const VgemmArgs& va, int64_t tile_cap, const float
 // Triangular product: tiles heaviest row first, dealt to the XCDs by column panels; the
 // reduction of a tile stops at its last row.
 // ---------------------------------------------------------------------------
+// (At most three workgroups per CU: enough to hide each other's waits, few enough that the
+// heaviest rows' tiles run first and the light ones fill in.  2500 x 1500, 960 tiles: 89
+// us, 94 at two, 95.5 with all of them resident at once; the vgemm above 135, 145, 139.)
 template <class C, bool WIDE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
 void k_trmm_f32(const float* __restrict__ l, int ldl, const float* __restrict__ b, int ldb, float* c, int ldc, int n,
                 int m, int tiles_m, int tiles_n) {
     extern __shared__ __attribute__((aligned(16))) float fsm[];
