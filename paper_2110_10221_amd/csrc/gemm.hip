@@ -771,11 +771,12 @@ hipError_t launch_linear(int dtype, const void* x, int ldx, const void* w, const
     }
     if (T == 0) return hipSuccess;
     if (dtype == 1) {
-        // the small tiles keep an operand tile's byte offsets below 2^31
-        if (ldx < 1 << 23 && K < 1 << 23) {
+        // these forms keep an operand tile's byte offsets (up to 256 rows) below 2^31
+        if (ldx < 1 << 22 && K < 1 << 22) {
             const LinearArgs a{static_cast<const uint16_t*>(x), ldx, static_cast<const uint16_t*>(w),
                                static_cast<const uint16_t*>(bias), static_cast<const uint16_t*>(residual), ldr,
                                static_cast<uint16_t*>(y), ldy, T, K, N};
+            if (gemm_big_wins(T, K, N, act, device_cu_count())) return launch_gemm_big(a, plan, s);
             if (const int which = small_gemm_choice(T, K, N, device_cu_count()))
                 return launch_gemm_small(which, act, a, plan, s);
         }

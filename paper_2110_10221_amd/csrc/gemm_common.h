@@ -152,6 +152,11 @@ struct LinearArgs {
 int small_gemm_choice(int64_t T, int64_t K, int64_t N, int64_t cus);
 hipError_t launch_gemm_small(int which, int act, const LinearArgs& a, const PlanView* plan, hipStream_t s);
 
+// 256 x 256 tiles for long reductions (gemm_big.hip): whether they are the faster ones, and
+// their launch (no activation).
+bool gemm_big_wins(int64_t T, int64_t K, int64_t N, int act, int64_t cus);
+hipError_t launch_gemm_big(const LinearArgs& a, const PlanView* plan, hipStream_t s);
+
 // fp32 launchers (gemm_f32.hip), called by the launchers that take both types.
 hipError_t launch_linear_f32(const float* x, int ldx, const float* w, const float* bias, const float* residual, int ldr,
                              int act, float* y, int ldy, int T, int K, int N, hipStream_t s);

@@ -73,3 +73,38 @@ def test_layer_builds_its_plan_in_a_small_launch(lengths, heads):
     for name, n in (("tok_off", None), ("att_off", None), ("order", None), ("tok_seq", T), ("av_items", 3 * n_av),
                     ("qkt_items", 4 * n_q), ("status", None)):
         assert torch.equal(getattr(plans[0], name)[:n], getattr(plans[1], name)[:n]), name
+
+
+@pytest.mark.parametrize("T,K,N,ldy_pad", [
+    (1300, 1536, 2112, 0),    # 54 tiles of 256 x 256, all as quarters, ragged both ways
+    (8300, 1600, 2112, 8),    # 256 whole tiles, then the quarters of 41; 25 steps of 64 k
+    (16384, 2048, 1024, 0),   # exactly one whole round
+    (16129, 1536, 960, 0),    # one round, its last tiles partial
+])
+@pytest.mark.parametrize("bias,res", [(True, True), (False, False)])
+def test_long_reductions(T, K, N, ldy_pad, bias, res):
+    import paper_2110_10221_amd as rag
+
+    rng = np.random.default_rng(T + K + N)
+    print(f"long-reduction linear T={T} K={K} N={N} bias={bias} res={res}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    xw = torch.full((T, K + 8), float("nan"), dtype=torch.bfloat16, device="cuda")  # NaN between the rows
+    xw[:, :K] = torch.randn(T, K, device="cuda", generator=gen).to(torch.bfloat16)
+    w = random_storage(rng, (N, K), "bf16", 0.05)
+    b = random_storage(rng, (N,), "bf16", 0.5) if bias else None
+    ld = N + ldy_pad
+    whole, yv = canary_buffer(T * ld, "bf16")
+    y = yv.view(T, ld)[:, :N]
+    rows = np.unique(np.r_[0:20, 120:136, 250:260, T // 2, T - 270:T - 250, T - 20:T])
+    r = None
+    if res:  # in place
+        y.copy_(torch.randn(T, N, device="cuda", generator=gen).to(torch.bfloat16))
+        r = host(y[rows], "bf16")
+    rag.packed_linear(xw[:, :K], dev(w, "bf16"), y, dev(b, "bf16") if bias else None, y if res else None)
+    torch.cuda.synchronize()
+    assert canary_intact(whole, T * ld)
+    if ldy_pad:
+        assert bool(torch.isnan(yv.view(T, ld)[:, N:].float()).all())
+    assert bool(torch.isfinite(y.float()).all())
+    ref = oracle.linear("bf16", host(xw[rows, :K], "bf16"), w, b, r, oracle.ACT_NONE)
+    assert close(host(y[rows], "bf16"), ref, "bf16")
