@@ -774,15 +774,20 @@ __device__ __forceinline__ float sum_xor32(float v) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-template <bool CAUSAL>
-__global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(4)))
+// KS = 2: two wave pairs per item, each walking half of the item's key chunks in LDS stages
+// of its own; the pairs' (reference, sum, output) states meet in LDS at the end.
+template <bool CAUSAL, int KS>
+__global__ __launch_bounds__(kStreamThreads * KS) __attribute__((amdgpu_waves_per_eu(4)))
 void k_attention_bf16(PlanArgs pa, const uint16_t* __restrict__ q, int ldq, const uint16_t* __restrict__ k,
                              int ldk, const uint16_t* __restrict__ v, int ldv, float scale,
                              uint16_t* __restrict__ O, int ldo) {
     if (pa.status[0] != 0) return;
-    __shared__ __attribute__((aligned(16))) uint16_t kvs[2 * kStreamStageElems];
+    __shared__ __attribute__((aligned(16))) uint16_t kvs_all[KS * 2 * kStreamStageElems];
     const int n_items = pa.status[2];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+    const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+    // the key half; the query half
+    const int part = KS == 1 ? 0 : wave_all / kStreamWaves, wave = KS == 1 ? wave_all : wave_all % kStreamWaves;
+    uint16_t* const kvs = kvs_all + part * 2 * kStreamStageElems;
     const int l32 = lane % 32, h2 = lane / 32;
     const int tr_e = (lane % 16) / 4, tr_q = lane % 4, tr_g = lane / 16;
     // A zero scale would turn the masked keys' -inf into NaN (-inf * 0); any
@@ -818,7 +823,10 @@ void k_attention_bf16(PlanArgs pa, const uint16_t* __restrict__ q, int ldq, cons
         const bool active = qb * 32 < L;
         const int nc_all = (L + 31) / 32;
         const int nc_wg = CAUSAL ? min(nc_all, 2 * ti + kStreamWaves) : nc_all;  // chunks the workgroup loads
-        const int nc_me = CAUSAL ? qb + 1 : nc_all;                    // chunks this wave uses
+        // this pair's chunks [c0, c1), and of those the ones this wave uses
+        const int nc_pair = KS == 1 ? nc_wg : (nc_wg + 1) / 2;
+        const int c0 = KS == 1 ? 0 : part * nc_pair, c1 = KS == 1 ? nc_wg : min(nc_wg, c0 + nc_pair);
+        const int nc_use = CAUSAL ? qb + 1 : nc_all, nc_me = KS == 1 ? nc_use : min(c1, nc_use);
         const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<uint16_t*>(k + (int64_t)t0 * ldk + h * kHeadDim), 0, (uint32_t)L * ldk * 2u, 0x00020000);
         const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(
@@ -868,7 +876,7 @@ void k_attention_bf16(PlanArgs pa, const uint16_t* __restrict__ q, int ldq, cons
             constexpr int STG = decltype(stg)::value;
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's copies of chunk c
             attn_barrier();  // ... and the other wave's; chunk c + 1's stage was last read in step c - 1
-            if (c + 1 < nc_wg) issue(c + 1, std::integral_constant<int, 1 - STG>{});
+            if (c + 1 < c1) issue(c + 1, std::integral_constant<int, 1 - STG>{});
             if (!active || c >= nc_me) return;
             const uint16_t* kst = kvs + STG * kStreamStageElems;
             floatx16 acc;
@@ -935,12 +943,12 @@ void k_attention_bf16(PlanArgs pa, const uint16_t* __restrict__ q, int ldq, cons
                 : "v"(vaddr[0][0]), "v"(vaddr[0][1]), "v"(vaddr[1][0]), "v"(vaddr[1][1]),
                   "i"(STG * kStreamStageElems * 2), "i"((STG * kStreamStageElems + 16 * kHeadDim) * 2)
                 : "memory");
-            if (c == 0) m = chunk_max();  // the reference starts at the first chunk's maximum
+            if (c == c0) m = chunk_max();  // the reference starts at the first chunk's maximum
             float ps = exps();
             // a lane sum above kSumCap (or NaN) means a score well above m: the wave
             // recomputes its scores, raises m to the chunk maximum and rescales what
             // it has summed so far (rare after the first chunks)
-            if (c > 0 && __ballot(!(ps <= kSumCap)) != 0) {
+            if (c > c0 && __ballot(!(ps <= kSumCap)) != 0) {
                 scores(std::true_type{});
                 const float mn = fmaxf(m, chunk_max());
                 const float alpha = __builtin_amdgcn_exp2f(m - mn);
@@ -974,12 +982,36 @@ void k_attention_bf16(PlanArgs pa, const uint16_t* __restrict__ q, int ldq, cons
             }
         };
         attn_barrier();  // both stages are free: the previous item's reads are done
-        issue(0, std::integral_constant<int, 0>{});
-        for (int c = 0; c < nc_wg; c += 2) {
-            step(c, std::integral_constant<int, 0>{});
-            if (c + 1 < nc_wg) step(c + 1, std::integral_constant<int, 1>{});
+        if (KS == 1 || c0 < c1) issue(c0, std::integral_constant<int, 0>{});
+        for (int i = 0; i < nc_pair; i += 2) {  // (the pairs step together: their barriers are shared)
+            step(c0 + i, std::integral_constant<int, 0>{});
+            if (i + 1 < nc_pair) step(c0 + i + 1, std::integral_constant<int, 1>{});
         }
-        if (active) {
+        if constexpr (KS == 2) {
+            attn_barrier();  // every wave is done with its stages
+            float* const mg = reinterpret_cast<float*>(kvs_all) + wave * (34 * kWave);
+            if (part == 1) {
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) mg[(cb * 16 + r) * kWave + lane] = oacc[cb][r];
+                mg[32 * kWave + lane] = m;
+                mg[33 * kWave + lane] = lsum;
+            }
+            attn_barrier();
+            if (part == 0 && active) {
+                // a pair with no chunk of its own has m = -inf and zero sums: weight 0
+                const float m1 = mg[32 * kWave + lane], mn = fmaxf(m, m1);
+                const float w0 = __builtin_amdgcn_exp2f(m - mn), w1 = __builtin_amdgcn_exp2f(m1 - mn);
+                lsum = lsum * w0 + mg[33 * kWave + lane] * w1;
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        oacc[cb][r] = oacc[cb][r] * w0 + mg[(cb * 16 + r) * kWave + lane] * w1;
+            }
+        }
+        if (part == 0 && active) {
             const float inv = 1.0f / sum_xor32(lsum);
             const int i = qb * 32 + l32;
             if (i < L) {
@@ -1089,7 +1121,13 @@ hipError_t launch_fused_variant(const PlanView& p, const void* q, int ldq, const
     const int64_t cap = std::max<int64_t>(p.av_cap, 1);
     const int64_t limit = (int64_t)device_cu_count() * kStreamPerCu;
     const int64_t g = (std::min(cap, limit) + kUnit - 1) / kUnit * kUnit;
-    hipLaunchKernelGGL(k_attention_bf16<CAUSAL>, dim3((unsigned)g), dim3(kStreamThreads), 0, s, plan_args(p),
+    // Two wave pairs per item where one item's chain of chunks is what the launch waits
+    // for: at least twenty chunks in the longest row and at most four items per CU (two
+    // sequences of 900..1024, 16 heads: 20.9 -> 16.2 us, masked 19.9 -> 14.3; but batch 32
+    // of 16..512, 1232 items, 17.2 -> 20.8: short items only pay for the merge).
+    const bool split = p.max_len >= 640 && cap <= 4 * (int64_t)device_cu_count();
+    auto* f = split ? &k_attention_bf16<CAUSAL, 2> : &k_attention_bf16<CAUSAL, 1>;
+    hipLaunchKernelGGL(f, dim3((unsigned)g), dim3(kStreamThreads * (split ? 2 : 1)), 0, s, plan_args(p),
                        static_cast<const uint16_t*>(q), ldq, static_cast<const uint16_t*>(k), ldk,
                        static_cast<const uint16_t*>(v), ldv, scale, static_cast<uint16_t*>(out), ldo);
     return hipGetLastError();

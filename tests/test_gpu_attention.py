@@ -329,3 +329,44 @@ def test_determinism_and_sequence_permutation():
     S1, P1, O1 = _run_unfused(L, H, q, k, v, "bf16", 0.125)
     S2, P2, O2 = _run_unfused(L, H, q, k, v, "bf16", 0.125)
     assert (S1 == S2).all() and (P1 == P2).all() and (O1 == O2).all()
+
+
+@pytest.mark.parametrize("L,H", [([1000, 641], 2), ([640, 1, 33, 700], 3), ([1024], 1)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_fused_attention_split_keys(L, H, causal):
+    # few items with long rows: two wave pairs share an item's key chunks (odd and even
+    # chunk counts, queries whose keys all lie in the first half, sequences of one chunk)
+    import paper_2110_10221_amd as rag
+
+    rng = np.random.default_rng(sum(L) + H)
+    L = np.array(L, np.int32)
+    T, d = int(L.sum()), H * 64
+    q, k, v = (random_storage(rng, (T, d), "bf16", 1.0) for _ in range(3))
+    plan = _plan(L, H)
+    print(f"split-key attention L={L.tolist()} H={H} causal={causal}", flush=True)
+    whole, O = canary_buffer(T * d, "bf16")
+    fn = rag.ragged_attention_causal if causal else rag.ragged_attention
+    fn(plan, dev(q, "bf16"), dev(k, "bf16"), dev(v, "bf16"), O.view(T, d), 0.125)
+    torch.cuda.synchronize()
+    assert not plan.data_errors() and canary_intact(whole, T * d)
+    qf, kf, vf = (values(a, "bf16") for a in (q, k, v))
+    got, t0 = values(host(O, "bf16"), "bf16").reshape(T, d), 0
+    for n in L:
+        for h in range(H):
+            c = slice(64 * h, 64 * h + 64)
+            s = 0.125 * qf[t0:t0 + n, c] @ kf[t0:t0 + n, c].T
+            if causal:
+                s[np.triu_indices(n, 1)] = -np.inf
+            p = np.exp(s - s.max(1, keepdims=True))
+            ref = (p / p.sum(1, keepdims=True)) @ vf[t0:t0 + n, c]
+            assert np.all(np.abs(got[t0:t0 + n, c] - ref) <= BF16_ATOL + BF16_RTOL * np.abs(ref) + 1e-3 * np.abs(ref).max())
+        t0 += int(n)
+
+
+@pytest.mark.parametrize("step", [16.0, 40.0])
+def test_fused_attention_split_keys_reference_raised(step):
+    # scores that rise with every chunk: the second half's reference far above the first's
+    L, H = np.array([900, 70], np.int32), 2
+    print(f"split-key attention, rising keys {step}", flush=True)
+    q, k, v = rising_keys(L, H, step, seed=int(step))
+    _fused_close(_fused(L, H, q, k, v, 0.125), L, H, q, k, v, 0.125)
