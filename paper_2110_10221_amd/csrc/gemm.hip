@@ -776,9 +776,10 @@ hipError_t launch_linear(int dtype, const void* x, int ldx, const void* w, const
             const LinearArgs a{static_cast<const uint16_t*>(x), ldx, static_cast<const uint16_t*>(w),
                                static_cast<const uint16_t*>(bias), static_cast<const uint16_t*>(residual), ldr,
                                static_cast<uint16_t*>(y), ldy, T, K, N};
-            if (gemm_big_wins(T, K, N, act, device_cu_count())) return launch_gemm_big(a, plan, s);
-            if (const int which = small_gemm_choice(T, K, N, device_cu_count()))
-                return launch_gemm_small(which, act, a, plan, s);
+            const int which = small_gemm_choice(T, K, N, device_cu_count());
+            if (which != kSmallWide && gemm_big_wins(T, K, N, act, device_cu_count()))
+                return launch_gemm_big(a, plan, s);
+            if (which != 0) return launch_gemm_small(which, act, a, plan, s);
         }
         if (act == 1) return launch_bf16_act<1>(x, ldx, w, bias, residual, ldr, y, ldy, T, K, N, plan, s);
         if (act == 2) return launch_bf16_act<2>(x, ldx, w, bias, residual, ldr, y, ldy, T, K, N, plan, s);

@@ -147,8 +147,9 @@ struct LinearArgs {
     int ldy, T, K, N;
 };
 
-// Smaller tiles for small launches (gemm_small.hip): the tile form to run (1 .. 4), or 0
+// Smaller tiles for small launches (gemm_small.hip): the tile form to run (1 .. 5), or 0
 // where the 128 x 256 tiles are estimated faster; and its launch.
+constexpr int kSmallWide = 5;  // 128 x 256 in one round: ahead of the 256 x 256 tiles too
 int small_gemm_choice(int64_t T, int64_t K, int64_t N, int64_t cus);
 hipError_t launch_gemm_small(int which, int act, const LinearArgs& a, const PlanView* plan, hipStream_t s);
 

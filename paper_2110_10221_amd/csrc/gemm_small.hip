@@ -1,7 +1,8 @@
 // bf16 packed linear operator for launches whose 128 x 256 tiles would leave the GPU
 // short of work: small token counts, or few output features with a long reduction.
 // The same product as gemm.hip, y = act(x w^T + bias) + residual, on smaller tiles:
-//   32 x 32, 64 x 64, 64 x 128 and 128 x 128 (tokens x features)
+//   32 x 32, 64 x 64, 64 x 128, 128 x 128 (tokens x features), and 128 x 256 where all
+//   of them run at once
 //  - What bounds it: a CU copies at most 64 bytes per cycle from L2 into LDS, and a
 //    T1 x T2 tile needs 2 (T1 + T2) bytes per k, so a 64 x 64 tile takes at least 1.7
 //    ns per k (2.4 GHz; 2.3 measured at 777 x 4096 x 1024) where its MFMAs take 0.8;
@@ -53,6 +54,7 @@ using Small32 = SmallCfg<32, 32, 1, 1, 4, 2, 4>;
 using Small64 = SmallCfg<64, 64, 1, 2, 2, 1, 4>;
 using Small128w = SmallCfg<64, 128, 1, 4, 2, 1, 3>;
 using Small128 = SmallCfg<128, 128, 2, 4, 1, 1, 3>;
+using Small256w = SmallCfg<128, 256, 2, 4, 1, 1, 3>;
 
 template <class C, int ACT>
 hipError_t launch_small(const LinearArgs& a, const PlanView* plan, hipStream_t s) {
@@ -77,6 +79,7 @@ hipError_t launch_small_act(int which, const LinearArgs& a, const PlanView* plan
         case 1: return launch_small<Small32, ACT>(a, plan, s);
         case 2: return launch_small<Small64, ACT>(a, plan, s);
         case 3: return launch_small<Small128w, ACT>(a, plan, s);
+        case 5: return launch_small<Small256w, ACT>(a, plan, s);
         default: return launch_small<Small128, ACT>(a, plan, s);
     }
 }
@@ -87,6 +90,14 @@ hipError_t launch_small_act(int which, const LinearArgs& a, const PlanView* plan
 // CU its reduction (us per 1024 k) and its prologue and epilogue.  The constants are
 // least-squares fits (6 to 12% rms) to calls timed at 224 shapes: T = 33 to 20000, K x
 // N of the projections of layers with d = 256 to 1024.
+// One range apart: with more 128 x 128 tiles than CUs but no more of 128 x 256, the
+// latter all run at once in eight waves of 64 x 64, a CU each, with three 64-k stages.
+// Their fit grows with the share of CUs at work (the clock falls), and against the other
+// forms long reductions gain (10076 x 2048 x 512 32.8 -> 27.8 us, 7000 x 4096 x 1024 64.2
+// -> 59.4, 10076 x 3072 x 768 53.5 -> 47.5, 1500 x 1024 x 4096 20.6 -> 17.9), short ones
+// do not (14000 x 512 x 512 14.0 -> 14.4): one workgroup per CU hides neither its first
+// loads nor its epilogue.  Nor where two rounds of 64 x 128 are all there is to do
+// (1310 x 1024 x 3072 12.8 -> 16.0), which the estimates show.
 int small_gemm_choice(int64_t T, int64_t K, int64_t N, int64_t cus) {
     struct Form {
         int64_t tm, tn;
@@ -94,10 +105,14 @@ int small_gemm_choice(int64_t T, int64_t K, int64_t N, int64_t cus) {
     };
     static constexpr Form kForms[] = {{32, 32, 3.1, 1.07, 0.8}, {64, 64, 2.9, 2.5, 0.94}, {64, 128, 2.1, 4.0, 1.7},
                                       {128, 128, 0.0, 5.85, 4.4}};
+    const int64_t n128 = (T + 127) / 128 * ((N + 127) / 128), n256 = (T + 127) / 128 * ((N + 255) / 256);
     double best = 0.0;
     int which = 0;
     for (int i = 0; i < 4; ++i) {
         const Form& f = kForms[i];
+        // 128 x 128 tiles would need two rounds here: timed, they never win
+        if (i == 3 && n128 > cus && n256 <= cus && K >= 1024 && 5.6 + (7.0 + 7.2 * n256 / cus) * 1e-3 * K < best)
+            return kSmallWide;
         const int64_t rounds = ((T + f.tm - 1) / f.tm * ((N + f.tn - 1) / f.tn) + cus - 1) / cus;
         const double c = f.start + rounds * (f.per_k * 1e-3 * K + f.tile);
         if (which == 0 || c < best) {

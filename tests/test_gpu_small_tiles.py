@@ -1,5 +1,5 @@
 """GPU parity of the bf16 linear operator's small-launch tiles (32 x 32, 64 x 64,
-64 x 128 and 128 x 128, chosen by the launch's size) at the edges of each: ragged
+64 x 128, 128 x 128 and 128 x 256 in one round, chosen by the launch's size) at the edges of each: ragged
 tokens, partial feature tiles, reductions of one 64-k block and of a number the
 stages do not divide, padded rows, in-place residuals; and the layer's plan built
 by such a launch."""
@@ -19,6 +19,7 @@ pytestmark = pytest.mark.gpu
     (1000, 512, 512), (777, 64, 1088), (1501, 256, 320), (2500, 320, 1600),       # 64 x 64
     (900, 192, 1600), (1700, 448, 832), (2236, 2048, 512),                         # 64 x 128
     (1300, 64, 2112), (3000, 192, 1088), (2236, 512, 1536),                        # 128 x 128
+    (4300, 1024, 960), (2000, 1088, 4032), (10241, 1216, 448),                     # 128 x 256, one round
 ])
 @pytest.mark.parametrize("act,res", [(oracle.ACT_NONE, True), (oracle.ACT_GELU_ERF, False)])
 def test_small_tiles(T, K, N, act, res):
@@ -44,7 +45,7 @@ def test_small_tiles(T, K, N, act, res):
 
 
 @pytest.mark.parametrize("lengths,heads", [([5, 70, 33], 2), ([64] * 40 + [3] * 100, 4), ([17] * 256, 8),
-                                           ([200, 1, 300] * 5, 8)])
+                                           ([200, 1, 300] * 5, 8), ([64] * 23 + [30], 16)])
 def test_layer_builds_its_plan_in_a_small_launch(lengths, heads):
     # the plan's workgroups behind each tile form: bit-identical to a plan built ahead
     import paper_2110_10221_amd as rag
