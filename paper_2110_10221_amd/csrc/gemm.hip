@@ -4,11 +4,11 @@
 // M = T and no padding).
 //
 // bf16: a 128 x 256 output tile per workgroup of 4 waves, each wave a 128
-// (tokens) x 64 (features) sub-tile of v_mfma_f32_32x32x16_bf16 accumulators
-// (the full-rate bf16 MFMA on gfx950).  A tile needs at most 80 KB of LDS, so two
-// workgroups share a CU and one's prologue / epilogue overlaps the other's K
-// loop.  (256-token tiles of 8 waves, measured against this design, were no
-// faster on 8192^3 and 8% slower on the QKV projection.)
+// (tokens) x 64 (features) sub-tile of v_mfma_f32_32x32x16_bf16 accumulators.
+// A tile needs at most 80 KB of LDS, so two workgroups share a CU and one's
+// prologue / epilogue overlaps the other's K loop.  (Long reductions without an
+// activation run on the 256 x 256 tiles of gemm_big.hip, small launches on those
+// of gemm_small.hip; launch_linear below holds the rule.)
 //  - Both operands are K-contiguous in memory (x is [T, K], w is [N, K]), the
 //    operand layout the MFMA wants, so tiles go to LDS untransposed.
 //  - Global -> LDS copies are bounds-checked buffer loads that write LDS
