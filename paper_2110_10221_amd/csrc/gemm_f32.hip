@@ -55,7 +55,8 @@ constexpr int kF32Out = 0x7ffffff0;  // a byte offset past every descriptor: rea
 //   W_KN  w is instead [K][N] (ldw): y = x w.
 //   TRI   x is lower triangular: x[i][k] counts only for k <= i (entries past the
 //         diagonal are dropped after they are read, so NaN there is harmless).
-// Rows of x and w must lie within 2^31 bytes of the tile's first (the caller checks).
+// Valid rows of x and w must lie within 2^31 bytes of the tile's first (the caller
+// checks); y may have any stride.
 template <class C, int ACT, bool WIDE, bool W_KN, bool TRI>
 __device__ __forceinline__ void gemm_tile_f32(const float* __restrict__ x, int ldx, const float* __restrict__ w,
                                               int ldw, const float* __restrict__ bias, const float* residual,
@@ -262,10 +263,15 @@ __device__ __forceinline__ void gemm_tile_f32(const float* __restrict__ x, int l
     }
     // Stores through a descriptor that ends with the tile's last valid row (rows past it
     // are dropped; features past N get an offset past the end), so no store is branched
-    // around.
+    // around.  A row past the last is dropped only if its 32-bit offset has not wrapped back
+    // into the descriptor, so every row of the tile, not only the valid ones, must lie
+    // within 2^31 bytes of the first; the rows of a wider stride are stored through 64-bit
+    // addresses instead.
     constexpr int kRegs = 16 / C::WK;  // accumulator registers this wave stores per block
     const int cols = min(N - n0, TN);
-    const __amdgpu_buffer_rsrc_t ry = make_rsrc(y + (int64_t)m0 * ldy + n0, (uint32_t)((rows_x - 1) * ldy + cols) * 4u);
+    const bool near = ((int64_t)(TM - 1) * ldy + cols) * 4 < kF32Out;
+    float* const yt = y + (int64_t)m0 * ldy + n0;
+    const __amdgpu_buffer_rsrc_t ry = make_rsrc(yt, near ? (uint32_t)((rows_x - 1) * ldy + cols) * 4u : 0u);
 #pragma unroll
     for (int i = 0; i < FN; ++i) {
         const int nl = wn * (TN / C::WN) + i * 32 + l32;
@@ -276,7 +282,7 @@ __device__ __forceinline__ void gemm_tile_f32(const float* __restrict__ x, int l
             // tile row of register r: its group is (r / 4) * WK + wk
             auto row = [&](int r) { return mb + 8 * ((r / 4) * C::WK + wk) + r % 4; };
             // the block's residuals are loaded before the first is used (rows clamped)
-            float rv[kRegs];
+            float o[kRegs], rv[kRegs];
             if (residual) {
 #pragma unroll
                 for (int r = 0; r < kRegs; ++r)
@@ -284,10 +290,18 @@ __device__ __forceinline__ void gemm_tile_f32(const float* __restrict__ x, int l
             }
 #pragma unroll
             for (int r = 0; r < kRegs; ++r) {
-                float o = activate<ACT>(acc[j][i][r] + bv);
-                if (residual) o += rv[r];
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o), ry, nl < cols ? (row(r) * ldy + nl) * 4 : kF32Out,
-                                                      0, 0);
+                o[r] = activate<ACT>(acc[j][i][r] + bv);
+                if (residual) o[r] += rv[r];
+            }
+            if (near) {
+#pragma unroll
+                for (int r = 0; r < kRegs; ++r)
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o[r]), ry,
+                                                          nl < cols ? (row(r) * ldy + nl) * 4 : kF32Out, 0, 0);
+            } else {
+#pragma unroll
+                for (int r = 0; r < kRegs; ++r)
+                    if (row(r) < rows_x && nl < cols) yt[(int64_t)row(r) * ldy + nl] = o[r];
             }
         }
     }
@@ -419,8 +433,7 @@ hipError_t launch_f32_tiles(const float* x, int ldx, const float* w, const float
 template <int ACT>
 hipError_t launch_linear_act(const float* x, int ldx, const float* w, const float* bias, const float* residual, int ldr,
                              float* y, int ldy, int T, int K, int N, hipStream_t s) {
-    if (!f32_reach(std::min(T, 128), ldx, K) || !f32_reach(std::min(N, 128), K, K) ||
-        !f32_reach(std::min(T, 128), ldy, N)) {
+    if (!f32_reach(std::min(T, 128), ldx, K) || !f32_reach(std::min(N, 128), K, K)) {
         hipLaunchKernelGGL((k_gemm_f32_far<ACT, false>), dim3((T + 63) / 64, (N + 63) / 64), dim3(256), 0, s, x, ldx, w,
                            K, bias, residual, ldr, y, ldy, T, K, N);
         return hipGetLastError();
@@ -532,7 +545,7 @@ hipError_t launch_vgemm_f32(const VgemmArgs& va, int64_t tile_cap, const float* 
 
 hipError_t launch_trmm_f32(const float* l, int ldl, const float* b, int ldb, float* c, int ldc, int n, int m,
                            hipStream_t s) {
-    if (!f32_reach(std::min(n, 128), ldl, n) || !f32_reach(kF32K, ldb, m) || !f32_reach(std::min(n, 128), ldc, m)) {
+    if (!f32_reach(std::min(n, 128), ldl, n) || !f32_reach(kF32K, ldb, m)) {
         hipLaunchKernelGGL((k_gemm_f32_far<0, true>), dim3((n + 63) / 64, (m + 63) / 64), dim3(256), 0, s, l, ldl, b,
                            ldb, nullptr, nullptr, 0, c, ldc, n, n, m);
         return hipGetLastError();

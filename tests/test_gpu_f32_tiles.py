@@ -62,6 +62,45 @@ def test_linear_rows_past_32_bit_offsets():
     assert close(host(c, "f32"), oracle.trmm("f32", T, N, L, B), "f32", N)
 
 
+def _strided(T, N, ld):
+    """[T, N] with leading dimension ld in a buffer of NaN, and the buffer."""
+    buf = torch.full((T, ld), float("nan"), device="cuda")
+    return buf, buf[:, :N]
+
+
+# Tile rows past the last one whose 32-bit store offset, row * ld * 4 mod 2^32, falls on a
+# valid row again (strides of 2^25 .. 2^27) or between the valid rows (the others).
+@pytest.mark.parametrize("T,K,N,ld", [(1, 64, 4096, 1 << 26), (1, 33, 4096, 1 << 27), (16, 32, 16384, 1 << 25),
+                                      (8, 32, 64, 60_000_000), (8, 36, 16384, 20_000_000), (70, 31, 9, 1 << 25)])
+def test_linear_output_stride_past_32_bit_offsets(T, K, N, ld):
+    import paper_2110_10221_amd as rag
+
+    rng = np.random.default_rng(T + K)
+    x, w = random_storage(rng, (T, K), "f32"), random_storage(rng, (N, K), "f32")
+    b, r = random_storage(rng, (N,), "f32"), random_storage(rng, (T, N), "f32")
+    print(f"f32 linear T={T} N={N}, ldy {ld}", flush=True)
+    buf, y = _strided(T, N, ld)
+    y.copy_(dev(r, "f32"))
+    rag.packed_linear(dev(x, "f32"), dev(w, "f32"), y, dev(b, "f32"), y, oracle.ACT_GELU_ERF)
+    torch.cuda.synchronize()
+    assert close(host(y, "f32"), oracle.linear("f32", x, w, b, r, oracle.ACT_GELU_ERF), "f32", N)
+    assert sum(int((~torch.isnan(row)).sum()) for row in buf) == T * N
+
+
+@pytest.mark.parametrize("n,m,ld", [(1, 64, 1 << 26), (4, 68, 1 << 26), (40, 68, 1 << 25), (8, 33, 60_000_000)])
+def test_trmm_output_stride_past_32_bit_offsets(n, m, ld):
+    import paper_2110_10221_amd as rag
+
+    rng = np.random.default_rng(n + m)
+    L, B = make_trmm_operands(n, m, rng, "f32")
+    print(f"trmm f32 n={n} m={m}, ldc {ld}", flush=True)
+    buf, c = _strided(n, m, ld)
+    rag.ragged_trmm(dev(L, "f32").view(n, n), dev(B, "f32").view(n, m), c)
+    torch.cuda.synchronize()
+    assert close(host(c, "f32"), oracle.trmm("f32", n, m, L, B), "f32", m)
+    assert sum(int((~torch.isnan(row)).sum()) for row in buf) == n * m
+
+
 @pytest.mark.parametrize("dims,sampled", [
     ([[64, 64, 64], [65, 63, 33], [3, 3, 1], [128, 256, 32], [130, 260, 36], [31, 1, 500]], False),
     ([[8320, 2048, 5], [130, 300, 64]], True),             # over 16 tiles per problem: 128 x 128 parts
