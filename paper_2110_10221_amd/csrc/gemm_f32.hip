@@ -54,7 +54,9 @@ constexpr int kF32Out = 0x7ffffff0;  // a byte offset past every descriptor: rea
 // (ldw), any K >= 0; called by the whole workgroup (256 threads), sm holds C::kLdsBytes.
 //   W_KN  w is instead [K][N] (ldw): y = x w.
 //   TRI   x is lower triangular: x[i][k] counts only for k <= i (entries past the
-//         diagonal are dropped after they are read, so NaN there is harmless).
+//         diagonal are dropped after they are read, so NaN there is harmless).  Zero times
+//         an infinity in w is not zero: a non-finite row k of w reaches the rows of y in
+//         its 64-row block, but none above (tiles of 128 rows drop w rows there too).
 // Valid rows of x and w must lie within 2^31 bytes of the tile's first (the caller
 // checks); y may have any stride.
 template <class C, int ACT, bool WIDE, bool W_KN, bool TRI>
@@ -68,6 +70,7 @@ __device__ __forceinline__ void gemm_tile_f32(const float* __restrict__ x, int l
     constexpr int kCopies = kXB + kWB;
     static_assert((ST - 1) * kCopies < 64, "the wait counter holds 63 loads");
     static_assert(!W_KN || TN >= 64, "the [K][N] swizzle moves columns by 32");
+    static_assert(!TRI || (W_KN && (TM == 64 || TM / C::WM == 64)), "64-row blocks of a triangular operand");
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
     const int l32 = lane % 32, h2 = lane / 32;
     const int wk = wave % C::WK, wm = wave / C::WK / C::WN, wn = wave / C::WK % C::WN;
@@ -146,6 +149,11 @@ __device__ __forceinline__ void gemm_tile_f32(const float* __restrict__ x, int l
             if constexpr (W_KN) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) b[i][e] = wst[(gq * 8 + 4 * h2 + e) * TN + (c ^ (h2 << 5))];
+                if constexpr (decltype(edge)::value && TM > 64) {
+                    const bool past = step * kF32K >= m0 + (wm + 1) * 64;  // the wave's last row
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) b[i][e] = past ? 0.f : b[i][e];
+                }
             } else {
                 b[i] = *reinterpret_cast<const floatx4*>(wst + c * kF32K + (((gq * 2 + h2) ^ swz2(c)) * 4));
             }
@@ -496,9 +504,13 @@ hipError_t launch_vgemm_tiles(const VgemmArgs& va, int64_t tile_cap, const float
 // ---------------------------------------------------------------------------
 // (At most three workgroups per CU: enough to hide each other's waits, few enough that the
 // heaviest rows' tiles run first and the light ones fill in.  2500 x 1500, 960 tiles: 89
-// us, 94 at two, 95.5 with all of them resident at once; the vgemm above 135, 145, 139.)
+// us, 94 at two, 95.5 with all of them resident at once; the vgemm above 135, 145, 139.
+// The LDS of 128 x 128 tiles allows two; registers for three would only spill.)
+template <class C>
+constexpr int kTrmmPerCu = C::kLdsBytes > 160 * 1024 / 3 ? 2 : 3;
+
 template <class C, bool WIDE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kTrmmPerCu<C>, kTrmmPerCu<C>)))
 void k_trmm_f32(const float* __restrict__ l, int ldl, const float* __restrict__ b, int ldb, float* c, int ldc, int n,
                 int m, int tiles_m, int tiles_n) {
     extern __shared__ __attribute__((aligned(16))) float fsm[];

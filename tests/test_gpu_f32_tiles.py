@@ -149,3 +149,24 @@ def test_trmm_tiles(n, m, pad):
     assert canary_intact(whole, n * m)
     rows = np.unique(np.r_[0:min(n, 40), n // 2, n - 2:n]) if n > 1000 else np.arange(n)
     assert close(host(c, "f32")[rows], oracle.trmm_rows("f32", n, m, L, B, rows), "f32", m)
+
+
+@pytest.mark.parametrize("n,m,r", [(4100, 4000, 3070), (200, 68, 100)])  # 128 x 128 tiles and 64 x 64 ones
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_trmm_row_of_infinities(n, m, r, bad):
+    # a non-finite row r of B reaches the rows of C from r on, and at most those of the
+    # 64-row block it lies in
+    import paper_2110_10221_amd as rag
+
+    rng = np.random.default_rng(r)
+    L, B = make_trmm_operands(n, m, rng, "f32")
+    print(f"trmm f32 n={n} m={m}, row {r} of B {bad}", flush=True)
+    Bd = dev(B, "f32").view(n, m)
+    Bd[r] = bad
+    c = torch.empty(n, m, device="cuda")
+    rag.ragged_trmm(dev(L, "f32").view(n, n), Bd, c)
+    torch.cuda.synchronize()
+    clean = r // 64 * 64
+    rows = np.arange(max(0, clean - 70), clean)
+    assert bool(torch.isfinite(c[:clean]).all()) and not bool(torch.isfinite(c[r:]).any())
+    assert close(host(c, "f32")[rows], oracle.trmm_rows("f32", n, m, L, B, rows), "f32", m)
