@@ -96,7 +96,9 @@ __device__ __forceinline__ void gemm_tile_f32(const float* __restrict__ x, int l
                 kl = ((((l32 >> 2)) ^ swz2(row)) << 2) + (l32 & 3);
             }
             const int k = step * kF32K + kl;
-            const int off = k < K ? (row * ld + k) * 4 : kF32Out;  // k < K: whole chunks when WIDE
+            // k < K: whole chunks when WIDE.  (The offset of a row past the last may wrap back
+            // into the range at strides of millions; what it reads there is never used.)
+            const int off = k < K ? (int)(((uint32_t)row * (uint32_t)ld + (uint32_t)k) * 4u) : kF32Out;
             copy_lds<WIDE ? 16 : 4>(r, dst + blk * kPer, off);
         };
         if (c < kXB) {
@@ -346,7 +348,7 @@ void k_gemm_f32(const float* __restrict__ x, int ldx, const float* __restrict__ 
 }
 
 // Operands whose rows the tile body's 32-bit byte offsets cannot reach (leading
-// dimensions of millions): 64 x 64 tiles of plain FMA with 64-bit addressing.
+// dimensions past 2^23): 64 x 64 tiles of plain FMA with 64-bit addressing.
 // [K][N] and triangular operands (TRI) as in the tile body above.
 template <int ACT, bool TRI>
 __global__ __launch_bounds__(256) void k_gemm_f32_far(const float* __restrict__ x, int64_t ldx,
@@ -433,7 +435,8 @@ hipError_t launch_f32_tiles(const float* x, int ldx, const float* w, const float
     };
     bool split_big, split_mid;
     const double big = cost(128, 4.0, 1.05, split_big), mid = cost(64, 1.05, 0.31, split_mid);
-    if (big <= mid)
+    // (leading dimensions between 2^22 and 2^23 reach 64 rows, but not 128)
+    if (big <= mid && f32_reach(std::min(T, 128), ldx, K) && f32_reach(std::min(N, 128), K, K))
         return launch_f32<F32Big, F32Mid, ACT, WIDE>(x, ldx, w, bias, residual, ldr, y, ldy, T, K, N, split_big, s);
     return launch_f32<F32Mid, F32Tiny, ACT, WIDE>(x, ldx, w, bias, residual, ldr, y, ldy, T, K, N, split_mid, s);
 }
@@ -441,7 +444,7 @@ hipError_t launch_f32_tiles(const float* x, int ldx, const float* w, const float
 template <int ACT>
 hipError_t launch_linear_act(const float* x, int ldx, const float* w, const float* bias, const float* residual, int ldr,
                              float* y, int ldy, int T, int K, int N, hipStream_t s) {
-    if (!f32_reach(std::min(T, 128), ldx, K) || !f32_reach(std::min(N, 128), K, K)) {
+    if (!f32_reach(std::min(T, 64), ldx, K) || !f32_reach(std::min(N, 64), K, K)) {
         hipLaunchKernelGGL((k_gemm_f32_far<ACT, false>), dim3((T + 63) / 64, (N + 63) / 64), dim3(256), 0, s, x, ldx, w,
                            K, bias, residual, ldr, y, ldy, T, K, N);
         return hipGetLastError();
@@ -557,14 +560,14 @@ hipError_t launch_vgemm_f32(const VgemmArgs& va, int64_t tile_cap, const float* 
 
 hipError_t launch_trmm_f32(const float* l, int ldl, const float* b, int ldb, float* c, int ldc, int n, int m,
                            hipStream_t s) {
-    if (!f32_reach(std::min(n, 128), ldl, n) || !f32_reach(kF32K, ldb, m)) {
+    if (!f32_reach(std::min(n, 64), ldl, n) || !f32_reach(kF32K, ldb, m)) {
         hipLaunchKernelGGL((k_gemm_f32_far<0, true>), dim3((n + 63) / 64, (m + 63) / 64), dim3(256), 0, s, l, ldl, b,
                            ldb, nullptr, nullptr, 0, c, ldc, n, n, m);
         return hipGetLastError();
     }
     const bool wide = n % 4 == 0 && m % 4 == 0 && ldl % 4 == 0 && ldb % 4 == 0 && al16(l) && al16(b);
     const int64_t big = (int64_t)((n + 127) / 128) * ((m + 127) / 128);
-    if (big >= 4 * (int64_t)device_cu_count())
+    if (big >= 4 * (int64_t)device_cu_count() && f32_reach(std::min(n, 128), ldl, n))
         return wide ? launch_trmm_tiles<F32Big, true>(l, ldl, b, ldb, c, ldc, n, m, s)
                     : launch_trmm_tiles<F32Big, false>(l, ldl, b, ldb, c, ldc, n, m, s);
     return wide ? launch_trmm_tiles<F32Mid, true>(l, ldl, b, ldb, c, ldc, n, m, s)

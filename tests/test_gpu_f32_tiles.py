@@ -41,10 +41,15 @@ def test_linear_any_shape(T, K, N, pad, shift):
     assert close(host(y, "f32")[rows], oracle.linear("f32", x[rows], w, b, r[rows], oracle.ACT_GELU_ERF), "f32", N)
 
 
-def test_linear_rows_past_32_bit_offsets():
+@pytest.mark.parametrize("T,K,N,ld", [
+    (70, 40, 9, 12_000_000),     # past 2^31 bytes within 64 rows: the plain-FMA kernel
+    (140, 64, 9, 8_000_000),     # within 128 rows only: 64 x 64 tiles
+    (300, 36, 2600, 5_000_001),  # the same on rows at any element
+    (3, 40, 9, 1 << 26),         # few rows: rows past the last whose offsets wrap
+])
+def test_linear_rows_past_32_bit_offsets(T, K, N, ld):
     import paper_2110_10221_amd as rag
 
-    T, K, N, ld = 70, 40, 9, 8_000_000                     # 69 rows reach past 2^31 bytes
     rng = np.random.default_rng(3)
     x, w = random_storage(rng, (T, K), "f32"), random_storage(rng, (N, K), "f32")
     print(f"f32 linear, ldx {ld}", flush=True)
