@@ -612,7 +612,8 @@ void k_gemm_bf16(const uint16_t* __restrict__ x, int ldx, const uint16_t* __rest
 
 // ---------------------------------------------------------------------------
 // Variable-sized batched GEMM: one workgroup per entry of the plan's tile list
-// (problems largest first).  The workgroup -> entry map deals the list to the
+// (problems largest first; LOOP: several, see vgemm_grid).  The map from workgroups to
+// entries deals the list to the
 // 8 XCDs in runs of consecutive entries (workgroups go to the XCDs round-robin),
 // so the tiles an XCD runs together mostly come from one problem and share its
 // operand panels in that XCD's L2, while every XCD still gets a share of the
@@ -631,21 +632,27 @@ __device__ __forceinline__ void vgemm_zero_tile(E* c, int m, int n, int m0, int 
         c[(int64_t)(m0 + e / cols) * n + n0 + e % cols] = E(0);
 }
 
+template <bool LOOP>
 __global__ __launch_bounds__(Cfg<kVgemmTileM>::kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_vgemm_bf16(VgemmArgs va, const uint16_t* __restrict__ a, const uint16_t* __restrict__ b, uint16_t* c, int run) {
     static_assert(kVgemmTileN == BN, "vgemm tiles are the GEMM's 128 x 256 tiles");
     extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
     if (!vgemm_ok(va, true)) return;
-    const int e = dealt_to_xcds(blockIdx.x, run);
-    if (e >= uni(va.status[1])) return;
-    const VgemmTile t = vgemm_tile(va, e);
-    uint16_t* cp = c + t.c_off;
-    if (t.k == 0) {
-        vgemm_zero_tile(cp, t.m, t.n, t.m0, t.n0, Cfg<kVgemmTileM>::kThreads);
-        return;
+    const int n = uni(va.status[1]);
+    for (int p = blockIdx.x; p - 8 * run < n; p += gridDim.x) {  // (position p holds entries past p - 8 run only)
+        const int e = dealt_to_xcds(p, run);
+        if (e < n) {
+            if (LOOP) barrier_lds();  // the previous tile is done with LDS
+            const VgemmTile t = vgemm_tile(va, e);
+            uint16_t* cp = c + t.c_off;
+            if (t.k == 0)
+                vgemm_zero_tile(cp, t.m, t.n, t.m0, t.n0, Cfg<kVgemmTileM>::kThreads);
+            else
+                gemm_tile_bf16<kVgemmTileM, 0, false, false>(a + t.a_off, t.k, b + t.b_off, nullptr, nullptr, 0, cp,
+                                                             t.n, t.m, t.k, t.n, t.m0, t.n0, smem);
+        }
+        if (!LOOP) return;
     }
-    gemm_tile_bf16<kVgemmTileM, 0, false, false>(a + t.a_off, t.k, b + t.b_off, nullptr, nullptr, 0, cp, t.n, t.m,
-                                                 t.k, t.n, t.m0, t.n0, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -717,16 +724,18 @@ hipError_t launch_vgemm(const VgemmView& p, int dtype, const void* a, int64_t a_
         constexpr int kLds = tile_lds_bytes<kVgemmTileM, false>();
         static bool attr_set = false;  // benign race: every thread sets the same value
         if (!attr_set) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_vgemm_bf16),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
-            if (e != hipSuccess) return e;
+            for (auto* f : {&k_vgemm_bf16<false>, &k_vgemm_bf16<true>}) {
+                hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(f),
+                                                   hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+                if (e != hipSuccess) return e;
+            }
             attr_set = true;
         }
         const int run = vgemm_run(p.tile_cap);
-        const int64_t quantum = 8 * run, grid = (p.tile_cap + quantum - 1) / quantum * quantum;
-        hipLaunchKernelGGL(k_vgemm_bf16, dim3((unsigned)grid), dim3(C::kThreads), kLds, s, va,
-                           static_cast<const uint16_t*>(a), static_cast<const uint16_t*>(b), static_cast<uint16_t*>(c),
-                           run);
+        const VgemmGrid g = vgemm_grid(p.tile_cap, 1, run, device_cu_count());
+        auto* f = g.loop ? &k_vgemm_bf16<true> : &k_vgemm_bf16<false>;
+        hipLaunchKernelGGL(f, dim3(g.blocks), dim3(C::kThreads), kLds, s, va, static_cast<const uint16_t*>(a),
+                           static_cast<const uint16_t*>(b), static_cast<uint16_t*>(c), run);
     } else {
         return launch_vgemm_f32(va, p.tile_cap, static_cast<const float*>(a), static_cast<const float*>(b),
                                 static_cast<float*>(c), s);

@@ -66,10 +66,12 @@ __device__ __forceinline__ bool trmm_tile_coords(int bid, int tiles_m, int tiles
     return true;
 }
 
-// List position of a workgroup when runs of `run` consecutive positions go to one XCD, the
-// runs round-robin; a permutation of [0, grid) when the grid is a multiple of 8 * run.
-__device__ __forceinline__ int dealt_to_xcds(int bid, int run) {
-    const int xcd = bid % 8, idx = bid / 8;
+// List position of work position p when runs of `run` consecutive list positions go to one
+// XCD (workgroups, and so positions taken with a stride that is a multiple of 8, go to the
+// XCDs round-robin), the runs round-robin; a permutation of [0, n) for any n that is a
+// multiple of 8 * run.
+__device__ __forceinline__ int dealt_to_xcds(int p, int run) {
+    const int xcd = p % 8, idx = p / 8;
     return ((idx / run) * 8 + xcd) * run + idx % run;
 }
 
@@ -157,6 +159,20 @@ hipError_t launch_gemm_small(int which, int act, const LinearArgs& a, const Plan
 // their launch (no activation).
 bool gemm_big_wins(int64_t T, int64_t K, int64_t N, int act, int64_t cus);
 hipError_t launch_gemm_big(const LinearArgs& a, const PlanView* plan, hipStream_t s);
+
+// Grid of a vgemm launch over `entries` list entries at most, `parts` workgroups each, dealt
+// in runs of `run` entries.  The list's length is known on the device only, and a plan's
+// capacity may be many times that (100,000 idle workgroups of 80 KB LDS take 70 us to come and
+// go): past kVgemmPerCu entries per CU the workgroups loop over the positions instead.
+constexpr int64_t kVgemmPerCu = 32;
+struct VgemmGrid {
+    int blocks;  // a multiple of 8
+    bool loop;
+};
+inline VgemmGrid vgemm_grid(int64_t entries, int64_t parts, int64_t run, int64_t cus) {
+    const int64_t all = (entries + 8 * run - 1) / (8 * run) * (8 * run) * parts, most = kVgemmPerCu * cus * parts / 8 * 8;
+    return all <= most ? VgemmGrid{(int)all, false} : VgemmGrid{(int)most, true};
+}
 
 // fp32 launchers (gemm_f32.hip), called by the launchers that take both types.
 hipError_t launch_linear_f32(const float* x, int ldx, const float* w, const float* bias, const float* residual, int ldr,

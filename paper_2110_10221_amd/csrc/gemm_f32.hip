@@ -455,49 +455,62 @@ hipError_t launch_linear_act(const float* x, int ldx, const float* w, const floa
 }
 
 // ---------------------------------------------------------------------------
-// Variable-sized batched GEMM: one workgroup per C-sized part of a list entry's
-// 128 x 256 tile; parts past the problem's edge exit at once.  Runs of `run` consecutive
-// entries go to one XCD (they mostly come from one problem and share its operand panels
-// in that L2), the runs round-robin.  Long runs leave some XCDs a run short at the end:
-// about 50 runs per XCD measured best (batch 32 of sizes 65..1023, 400 entries: 139 us
+// Variable-sized batched GEMM: one workgroup per C-sized part of a list entry's 128 x 256
+// tile (LOOP: several, see vgemm_grid); parts past the problem's edge end at once.  Runs of
+// `run` consecutive entries go to one XCD (they mostly come from one problem and share its
+// operand panels in that L2), the runs round-robin.  Long runs leave some XCDs a run short at
+// the end: about 50 runs per XCD measured best (batch 32 of sizes 65..1023, 400 entries: 139 us
 // at one entry per run, 154 at 4, 162 at 16; sizes 512..1408, 900 entries: 475 at 2, 504 at 16).
 // ---------------------------------------------------------------------------
 template <class C>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
+constexpr int kPerCu = C::kLdsBytes > 160 * 1024 / 3 ? 2 : 3;  // workgroups per CU of vgemm and trmm
+
+template <class C, bool LOOP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPerCu<C>, kPerCu<C>)))
 void k_vgemm_f32(VgemmArgs va, const float* __restrict__ a, const float* __restrict__ b, float* c, int run) {
     constexpr int kPm = kVgemmTileM / C::TM, kParts = kPm * (kVgemmTileN / C::TN);
     extern __shared__ __attribute__((aligned(16))) float fsm[];
     if (!vgemm_ok(va, false)) return;
-    const int part = dealt_to_xcds(blockIdx.x, run * kParts), e = part / kParts, sub = part % kParts;
-    if (e >= uni(va.status[1])) return;
-    const VgemmTile t = vgemm_tile(va, e);
-    const int m0 = t.m0 + sub % kPm * C::TM, n0 = t.n0 + sub / kPm * C::TN;
-    if (m0 >= t.m || n0 >= t.n) return;
-    const float *ap = a + t.a_off, *bp = b + t.b_off;
-    const bool wide = (t.k & 3) == 0 && ((reinterpret_cast<uintptr_t>(ap) | reinterpret_cast<uintptr_t>(bp)) & 15) == 0;
-    if (wide)
-        gemm_tile_f32<C, 0, true, false, false>(ap, t.k, bp, t.k, nullptr, nullptr, 0, c + t.c_off, t.n, t.m, t.k, t.n,
-                                                m0, n0, fsm);
-    else
-        gemm_tile_f32<C, 0, false, false, false>(ap, t.k, bp, t.k, nullptr, nullptr, 0, c + t.c_off, t.n, t.m, t.k,
-                                                 t.n, m0, n0, fsm);
+    const int n = uni(va.status[1]), runs = run * kParts;
+    // (a batch that fits in memory has under 2^23 entries)
+    for (int p = blockIdx.x; p - 8 * runs < n * kParts; p += gridDim.x) {  // (position p holds parts past p - 8 runs)
+        const int part = dealt_to_xcds(p, runs), e = part / kParts, sub = part % kParts;
+        if (e < n) {
+            const VgemmTile t = vgemm_tile(va, e);
+            const int m0 = t.m0 + sub % kPm * C::TM, n0 = t.n0 + sub / kPm * C::TN;
+            if (m0 < t.m && n0 < t.n) {
+                if (LOOP) barrier_lds();  // the previous part is done with LDS
+                const float *ap = a + t.a_off, *bp = b + t.b_off;
+                const bool wide =
+                    (t.k & 3) == 0 && ((reinterpret_cast<uintptr_t>(ap) | reinterpret_cast<uintptr_t>(bp)) & 15) == 0;
+                if (wide)
+                    gemm_tile_f32<C, 0, true, false, false>(ap, t.k, bp, t.k, nullptr, nullptr, 0, c + t.c_off, t.n,
+                                                            t.m, t.k, t.n, m0, n0, fsm);
+                else
+                    gemm_tile_f32<C, 0, false, false, false>(ap, t.k, bp, t.k, nullptr, nullptr, 0, c + t.c_off, t.n,
+                                                             t.m, t.k, t.n, m0, n0, fsm);
+            }
+        }
+        if (!LOOP) return;
+    }
 }
 
 template <class C>
 hipError_t launch_vgemm_tiles(const VgemmArgs& va, int64_t tile_cap, const float* a, const float* b, float* c,
                               hipStream_t s) {
-    constexpr int64_t kParts = (kVgemmTileM / C::TM) * (kVgemmTileN / C::TN);
-    const int run = (int)std::min<int64_t>(16, std::max<int64_t>(1, tile_cap / 400));
-    const int64_t quantum = 8 * run * kParts;
     static bool attr_set = false;  // benign race: every thread sets the same value
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_vgemm_f32<C>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, C::kLdsBytes);
-        if (e != hipSuccess) return e;
+        for (auto* f : {&k_vgemm_f32<C, false>, &k_vgemm_f32<C, true>}) {
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(f),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, C::kLdsBytes);
+            if (e != hipSuccess) return e;
+        }
         attr_set = true;
     }
-    const int64_t grid = (tile_cap * kParts + quantum - 1) / quantum * quantum;
-    hipLaunchKernelGGL(k_vgemm_f32<C>, dim3((unsigned)grid), dim3(256), C::kLdsBytes, s, va, a, b, c, run);
+    const int run = (int)std::min<int64_t>(16, std::max<int64_t>(1, tile_cap / 400));
+    const VgemmGrid g = vgemm_grid(tile_cap, (kVgemmTileM / C::TM) * (kVgemmTileN / C::TN), run, device_cu_count());
+    auto* f = g.loop ? &k_vgemm_f32<C, true> : &k_vgemm_f32<C, false>;
+    hipLaunchKernelGGL(f, dim3(g.blocks), dim3(256), C::kLdsBytes, s, va, a, b, c, run);
     return hipGetLastError();
 }
 
@@ -509,11 +522,8 @@ hipError_t launch_vgemm_tiles(const VgemmArgs& va, int64_t tile_cap, const float
 // heaviest rows' tiles run first and the light ones fill in.  2500 x 1500, 960 tiles: 89
 // us, 94 at two, 95.5 with all of them resident at once; the vgemm above 135, 145, 139.
 // The LDS of 128 x 128 tiles allows two; registers for three would only spill.)
-template <class C>
-constexpr int kTrmmPerCu = C::kLdsBytes > 160 * 1024 / 3 ? 2 : 3;
-
 template <class C, bool WIDE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kTrmmPerCu<C>, kTrmmPerCu<C>)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kPerCu<C>, kPerCu<C>)))
 void k_trmm_f32(const float* __restrict__ l, int ldl, const float* __restrict__ b, int ldb, float* c, int ldc, int n,
                 int m, int tiles_m, int tiles_n) {
     extern __shared__ __attribute__((aligned(16))) float fsm[];

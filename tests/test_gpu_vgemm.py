@@ -135,6 +135,45 @@ def test_loose_tile_cap():
     assert np.array_equal(exact, loose)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("tile_cap", [40, 3_000_000])
+def test_capacity_of_any_size(dtype, tile_cap):
+    # at 3,000,000 entries one fp32 workgroup per 64 x 64 part would pass the 2^32 work
+    # items a launch can have
+    dims = np.array([[200, 264, 128], [64, 512, 64], [3, 8, 0]], np.int32)
+    rng = np.random.default_rng(6)
+    a, b = make_vgemm_operands(dims, rng, dtype)
+    print(f"vgemm {dtype} tile_cap={tile_cap}", flush=True)
+    _check_products(_run(dims, a, b, dtype, tile_cap=tile_cap), dims, a, b, dtype)
+
+
+@pytest.mark.parametrize("dtype,B,m,n,k", [
+    ("bf16", 1500, 300, 264, 64),   # 9000 entries: over 32 per CU, the workgroups loop
+    ("f32", 1500, 300, 262, 33),    # 9000 entries in 64 x 64 parts
+    ("f32", 600, 1000, 500, 36),    # 9600 entries in 128 x 128 parts
+])
+def test_list_longer_than_the_grid(dtype, B, m, n, k):
+    import paper_2110_10221_amd as rag
+
+    dims = np.tile(np.array([[m, n, k]], np.int32), (B, 1))
+    print(f"vgemm {dtype} {B} x {m} x {n} x {k}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(B + n)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    a = torch.randn(B, m, k, device="cuda", generator=gen).to(dt)
+    b = torch.randn(B, n, k, device="cuda", generator=gen).to(dt)
+    plan = _plan(dims)
+    whole, c = canary_buffer(B * m * n, dtype)
+    rag.ragged_vgemm(plan, a.view(-1), b.view(-1), c)
+    torch.cuda.synchronize()
+    assert not plan.data_errors() and plan.n_tiles() > 8192 and canary_intact(whole, B * m * n)
+    # against fp64: one rounding to the storage type of sums of k products of order one
+    tol = 2.0 ** -8 if dtype == "bf16" else 1e-5
+    for p0 in range(0, B, 100):
+        ref = torch.bmm(a[p0:p0 + 100].double(), b[p0:p0 + 100].double().transpose(1, 2).contiguous())
+        err = (c.view(B, m, n)[p0:p0 + 100].double() - ref).abs()
+        assert bool((err <= tol * ref.abs() + 1e-5 * k).all()), p0
+
+
 def test_bf16_shape_rule_and_operand_capacity():
     import paper_2110_10221_amd as rag
 
