@@ -617,12 +617,17 @@ void k_gemm_bf16(const uint16_t* __restrict__ x, int ldx, const uint16_t* __rest
 // 8 XCDs in runs of consecutive entries (workgroups go to the XCDs round-robin),
 // so the tiles an XCD runs together mostly come from one problem and share its
 // operand panels in that XCD's L2, while every XCD still gets a share of the
-// large problems first.  At 3869 entries runs of 32 measured best (8, 16 and 64
-// 1-5% slower); shorter lists take shorter runs, at least 15 per XCD, or some
-// XCDs would be a run short (or idle) at the end: batch 6 of sizes 128..768 14.6 ->
-// 11.6 us, batch 23 of 128..640 15.6 -> 14.4.
+// large problems first.  Problems of a dozen entries or more on average (by the plan's
+// capacity) take runs of 16: 206 entries of 10 problems 25.5 us (27.2 at 8, 30.2 at one, 26.2
+// at 32), 478 of 32 30.7 (32.5, 43.0, 30.8), 8192^3 907 (899, 895, 939); long lists of such
+// problems up to 32, where anything from 12 on is within 2%.  Smaller problems take runs of
+// 8: 201 entries of 128 problems 8.8 us (9.2 at 16, 10.3 at 32), and short lists runs that
+// leave no XCD idle (49 entries: 12.2 at 4, 12.8 at 16, 14.9 at 32).
 // ---------------------------------------------------------------------------
-int vgemm_run(int64_t tile_cap) { return (int)std::min<int64_t>(32, std::max<int64_t>(1, tile_cap / 120)); }
+int vgemm_run(int64_t entries, int64_t batch) {
+    const int64_t run = entries < 12 * batch ? 8 : std::min<int64_t>(32, std::max<int64_t>(16, entries / 120));
+    return (int)std::min(run, std::max<int64_t>(1, entries / 12));
+}
 
 // C = 0 over the rows [m0, m) x columns [n0, n) of a tile (problems with k = 0).
 template <typename E>
@@ -731,7 +736,7 @@ hipError_t launch_vgemm(const VgemmView& p, int dtype, const void* a, int64_t a_
             }
             attr_set = true;
         }
-        const int run = vgemm_run(p.tile_cap);
+        const int run = vgemm_run(p.tile_cap, p.batch);
         const VgemmGrid g = vgemm_grid(p.tile_cap, 1, run, device_cu_count());
         auto* f = g.loop ? &k_vgemm_bf16<true> : &k_vgemm_bf16<false>;
         hipLaunchKernelGGL(f, dim3(g.blocks), dim3(C::kThreads), kLds, s, va, static_cast<const uint16_t*>(a),

@@ -456,11 +456,11 @@ hipError_t launch_linear_act(const float* x, int ldx, const float* w, const floa
 
 // ---------------------------------------------------------------------------
 // Variable-sized batched GEMM: one workgroup per C-sized part of a list entry's 128 x 256
-// tile (LOOP: several, see vgemm_grid); parts past the problem's edge end at once.  Runs of
-// `run` consecutive entries go to one XCD (they mostly come from one problem and share its
-// operand panels in that L2), the runs round-robin.  Long runs leave some XCDs a run short at
-// the end: about 50 runs per XCD measured best (batch 32 of sizes 65..1023, 400 entries: 139 us
-// at one entry per run, 154 at 4, 162 at 16; sizes 512..1408, 900 entries: 475 at 2, 504 at 16).
+// tile (LOOP: several, see vgemm_grid); parts past the problem's edge end at once.  The
+// entries go to the XCDs round-robin, an entry's parts to one: these tiles wait for the matrix
+// cores, not for their operands, and any unevenness shows (369 entries of sizes 512..1408: 182
+// us, 205 in runs of two, 213 of four); from 1600 entries on, where it averages out, runs of
+// four (2279 to 7259 entries: at most 3% between one and 16).
 // ---------------------------------------------------------------------------
 template <class C>
 constexpr int kPerCu = C::kLdsBytes > 160 * 1024 / 3 ? 2 : 3;  // workgroups per CU of vgemm and trmm
@@ -507,7 +507,7 @@ hipError_t launch_vgemm_tiles(const VgemmArgs& va, int64_t tile_cap, const float
         }
         attr_set = true;
     }
-    const int run = (int)std::min<int64_t>(16, std::max<int64_t>(1, tile_cap / 400));
+    const int run = tile_cap < 1600 ? 1 : 4;
     const VgemmGrid g = vgemm_grid(tile_cap, (kVgemmTileM / C::TM) * (kVgemmTileN / C::TN), run, device_cu_count());
     auto* f = g.loop ? &k_vgemm_f32<C, true> : &k_vgemm_f32<C, false>;
     hipLaunchKernelGGL(f, dim3(g.blocks), dim3(256), C::kLdsBytes, s, va, a, b, c, run);
