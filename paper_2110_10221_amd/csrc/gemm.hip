@@ -8,7 +8,7 @@
 // A tile needs at most 80 KB of LDS, so two workgroups share a CU and one's
 // prologue / epilogue overlaps the other's K loop.  (Long reductions without an
 // activation run on the 256 x 256 tiles of gemm_big.hip, small launches on those
-// of gemm_small.hip; launch_linear below holds the rule.)
+// of gemm_small.hip; linear_form_bf16 holds the rule.)
 //  - Both operands are K-contiguous in memory (x is [T, K], w is [N, K]), the
 //    operand layout the MFMA wants, so tiles go to LDS untransposed.
 //  - Global -> LDS copies are bounds-checked buffer loads that write LDS
@@ -790,10 +790,9 @@ hipError_t launch_linear(int dtype, const void* x, int ldx, const void* w, const
             const LinearArgs a{static_cast<const uint16_t*>(x), ldx, static_cast<const uint16_t*>(w),
                                static_cast<const uint16_t*>(bias), static_cast<const uint16_t*>(residual), ldr,
                                static_cast<uint16_t*>(y), ldy, T, K, N};
-            const int which = small_gemm_choice(T, K, N, device_cu_count());
-            if (which != kSmallWide && gemm_big_wins(T, K, N, act, device_cu_count()))
-                return launch_gemm_big(a, plan, s);
-            if (which != 0) return launch_gemm_small(which, act, a, plan, s);
+            const int form = linear_form_bf16(T, K, N, act, device_cu_count());
+            if (form == kFormBig) return launch_gemm_big(a, plan, s);
+            if (form != 0) return launch_gemm_small(form, act, a, plan, s);
         }
         if (act == 1) return launch_bf16_act<1>(x, ldx, w, bias, residual, ldr, y, ldy, T, K, N, plan, s);
         if (act == 2) return launch_bf16_act<2>(x, ldx, w, bias, residual, ldr, y, ldy, T, K, N, plan, s);

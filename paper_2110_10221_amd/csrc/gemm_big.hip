@@ -228,14 +228,26 @@ void k_gemm_big(const uint16_t* __restrict__ x, int ldx, const uint16_t* __restr
 
 }  // namespace
 
+// Whole tiles where a launch has nearly a round of them or more; else its last, partial round,
+// which may be all of it, runs as quarters.
+static int64_t big_whole_tiles(int64_t tiles, int64_t cus) {
+    const int64_t rest = tiles % cus;
+    return 4 * rest > 3 * cus ? tiles : tiles - rest;  // nearly full: quarters would take as long
+}
+
 // Long reductions only (sixteen 64-k steps barely pay for the exposed epilogue: of 162
 // timed shapes, T = 2236 to 35475, those with K >= 1536 ran 1-12% faster than on the other
-// tiles and nearly all shorter ones slower), without an activation, and with enough
-// quarters for the CUs: at least five for eight CUs, and not the range where a second
-// round of quarters would be nearly empty (0.95-1.01x there).
+// tiles and nearly all shorter ones slower), without an activation, and with enough for the
+// CUs to do.  A launch of quarters alone, counting those with a token and a feature of their
+// own (100 x 4096 x 12288 has 96 such and ran 28.7 us, 23.3 on 64 x 128 tiles; at 32 x 4096 x
+// 16384 34.9 against 21.5), needs five for eight CUs and no second or third round that
+// would be nearly empty (0.95-1.01x there, 0.96-0.98x at 657 x 1536..4096 x 12992).
 bool gemm_big_wins(int64_t T, int64_t K, int64_t N, int act, int64_t cus) {
-    const int64_t quarters = 4 * ((T + 255) / 256) * ((N + 255) / 256);
-    return act == 0 && K >= 1536 && 8 * quarters >= 5 * cus && (quarters <= cus || 10 * quarters >= 13 * cus);
+    if (act != 0 || K < 1536) return false;
+    if (big_whole_tiles(((T + 255) / 256) * ((N + 255) / 256), cus) > 0) return true;
+    const int64_t quarters = ((T + 127) / 128) * ((N + 127) / 128);
+    return 8 * quarters >= 5 * cus && (quarters <= cus || 10 * quarters >= 13 * cus) &&
+           (quarters <= 2 * cus || 5 * quarters >= 12 * cus);
 }
 
 hipError_t launch_gemm_big(const LinearArgs& a, const PlanView* plan, hipStream_t s) {
@@ -248,8 +260,7 @@ hipError_t launch_gemm_big(const LinearArgs& a, const PlanView* plan, hipStream_
     }
     const int cus = device_cu_count();
     const int tiles_m = (a.T + 255) / 256, tiles_n = (a.N + 255) / 256, tiles = tiles_m * tiles_n;
-    const int rest = tiles % cus;
-    const int n_full = 4 * rest > 3 * cus ? tiles : tiles - rest;  // nearly full: quarters would take as long
+    const int n_full = (int)big_whole_tiles(tiles, cus);
     const int n_gemm = n_full + 4 * (tiles - n_full);
     const PlanFillArgs pf = plan ? plan_fill_args(*plan) : PlanFillArgs{};
     hipLaunchKernelGGL(k_gemm_big, dim3(n_gemm + (plan ? plan->batch : 0)), dim3(BigCfg::kThreads), BigCfg::kLds, s, a.x,

@@ -149,16 +149,14 @@ struct LinearArgs {
     int ldy, T, K, N;
 };
 
-// Smaller tiles for small launches (gemm_small.hip): the tile form to run (1 .. 5), or 0
-// where the 128 x 256 tiles are estimated faster; and its launch.
-constexpr int kSmallWide = 5;  // 128 x 256 in one round: ahead of the 256 x 256 tiles too
-int small_gemm_choice(int64_t T, int64_t K, int64_t N, int64_t cus);
-hipError_t launch_gemm_small(int which, int act, const LinearArgs& a, const PlanView* plan, hipStream_t s);
-
-// 256 x 256 tiles for long reductions (gemm_big.hip): whether they are the faster ones, and
-// their launch (no activation).
+// The tile form a bf16 packed linear call runs, by its sizes: 0 the 128 x 256 tiles
+// (gemm.hip), 1 .. 4 smaller tiles for small launches and 5 128 x 256 in one round
+// (gemm_small.hip), 6 256 x 256 for long reductions (gemm_big.hip).
+constexpr int kFormWide = 5, kFormBig = 6;
+int linear_form_bf16(int64_t T, int64_t K, int64_t N, int act, int64_t cus);
+hipError_t launch_gemm_small(int form, int act, const LinearArgs& a, const PlanView* plan, hipStream_t s);
 bool gemm_big_wins(int64_t T, int64_t K, int64_t N, int act, int64_t cus);
-hipError_t launch_gemm_big(const LinearArgs& a, const PlanView* plan, hipStream_t s);
+hipError_t launch_gemm_big(const LinearArgs& a, const PlanView* plan, hipStream_t s);  // no activation
 
 // Grid of a vgemm launch over `entries` list entries at most, `parts` workgroups each, dealt
 // in runs of `run` entries.  The list's length is known on the device only, and a plan's

@@ -7,7 +7,7 @@
 //    T1 x T2 tile needs 2 (T1 + T2) bytes per k, so a 64 x 64 tile takes at least 1.7
 //    ns per k (2.4 GHz; 2.3 measured at 777 x 4096 x 1024) where its MFMAs take 0.8;
 //    larger tiles need fewer bytes per product but leave CUs idle.  The launch picks
-//    the tile whose busiest CU finishes first (tile_cost below).
+//    the tile whose busiest CU finishes first (small_gemm_choice below).
 //  - Both operands are staged 64 k deep, one 128-byte row per token or feature, so
 //    every copy request is a whole line (64-byte rows: 21 against 35 TB/s from L2),
 //    3 or 4 stages ahead: a small launch reads mostly from the Infinity Cache, whose
@@ -98,7 +98,7 @@ hipError_t launch_small_act(int which, const LinearArgs& a, const PlanView* plan
 // do not (14000 x 512 x 512 14.0 -> 14.4): one workgroup per CU hides neither its first
 // loads nor its epilogue.  Nor where two rounds of 64 x 128 are all there is to do
 // (1310 x 1024 x 3072 12.8 -> 16.0), which the estimates show.
-int small_gemm_choice(int64_t T, int64_t K, int64_t N, int64_t cus) {
+static int small_gemm_choice(int64_t T, int64_t K, int64_t N, int64_t cus) {
     struct Form {
         int64_t tm, tn;
         double start, per_k, tile;
@@ -112,7 +112,7 @@ int small_gemm_choice(int64_t T, int64_t K, int64_t N, int64_t cus) {
         const Form& f = kForms[i];
         // 128 x 128 tiles would need two rounds here: timed, they never win
         if (i == 3 && n128 > cus && n256 <= cus && K >= 1024 && 5.6 + (7.0 + 7.2 * n256 / cus) * 1e-3 * K < best)
-            return kSmallWide;
+            return kFormWide;
         const int64_t rounds = ((T + f.tm - 1) / f.tm * ((N + f.tn - 1) / f.tn) + cus - 1) / cus;
         const double c = f.start + rounds * (f.per_k * 1e-3 * K + f.tile);
         if (which == 0 || c < best) {
@@ -130,10 +130,15 @@ int small_gemm_choice(int64_t T, int64_t K, int64_t N, int64_t cus) {
     return best < 0.9 * (4.7 + rounds * (12.9e-3 * K + 2.7)) ? which : 0;
 }
 
-hipError_t launch_gemm_small(int which, int act, const LinearArgs& a, const PlanView* plan, hipStream_t s) {
-    if (act == 1) return launch_small_act<1>(which, a, plan, s);
-    if (act == 2) return launch_small_act<2>(which, a, plan, s);
-    return launch_small_act<0>(which, a, plan, s);
+int linear_form_bf16(int64_t T, int64_t K, int64_t N, int act, int64_t cus) {
+    const int form = small_gemm_choice(T, K, N, cus);
+    return form != kFormWide && gemm_big_wins(T, K, N, act, cus) ? kFormBig : form;
+}
+
+hipError_t launch_gemm_small(int form, int act, const LinearArgs& a, const PlanView* plan, hipStream_t s) {
+    if (act == 1) return launch_small_act<1>(form, a, plan, s);
+    if (act == 2) return launch_small_act<2>(form, a, plan, s);
+    return launch_small_act<0>(form, a, plan, s);
 }
 
 }  // namespace rag

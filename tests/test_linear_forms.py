@@ -1,0 +1,40 @@
+"""The tile form a bf16 packed linear call takes (host arithmetic, no GPU needed), at
+sizes where every form was timed: the rule must not name one measured slower."""
+import ctypes
+import os
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_2110_10221_amd", "libragged.so")
+needs_lib = pytest.mark.skipif(not os.path.exists(LIB), reason="libragged.so not built")
+
+CUS = 256
+# 0: 128 x 256 tiles, two per CU; 1 .. 4: 32 x 32, 64 x 64, 64 x 128, 128 x 128; 5: 128 x 256,
+# one round; 6: 256 x 256 (and 128 x 128 quarters)
+
+
+def form(T, K, N, act=0):
+    import paper_2110_10221_amd as rag
+
+    f = rag.library()._ZN3rag16linear_form_bf16Elllil  # rag::linear_form_bf16
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int64] * 3 + [ctypes.c_int, ctypes.c_int64]
+    return f(T, K, N, act, CUS)
+
+
+@needs_lib
+@pytest.mark.parametrize("T,K,N,forms", [
+    # few tokens: most of a 128-row quarter is empty (us, best of the small tiles / 256 x 256)
+    (1, 4224, 14272, (1, 2)),      # 18.7 / 26.5
+    (8, 3968, 13760, (1, 2)),      # 17.6 / 25.1
+    (32, 4096, 16384, (1, 2)),     # 21.5 / 34.9
+    (100, 4096, 12288, (2, 3)),    # 23.3 / 28.7
+    (257, 4096, 5120, (2, 3)),     # 21.9 / 29.2
+    # enough of them: the 256 x 256 kernel
+    (1300, 1536, 2112, (6,)), (5200, 2048, 512, (6,)),          # 18.9 / 17.7
+    (4000, 4096, 1024, (6,)), (2000, 2048, 4992, (6,)),         # 54.9 (form 0) / 53.1
+    (16384, 2048, 1024, (6,)), (35475, 4096, 1024, (6,)),       # 68.8 / 62.7, 298 / 270
+    (10076, 2048, 512, (5,)), (35475, 1024, 4096, (0,)),
+])
+def test_long_reduction_form(T, K, N, forms):
+    assert form(T, K, N) in forms
