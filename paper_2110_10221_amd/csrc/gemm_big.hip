@@ -240,14 +240,13 @@ static int64_t big_whole_tiles(int64_t tiles, int64_t cus) {
 // tiles and nearly all shorter ones slower), without an activation, and with enough for the
 // CUs to do.  A launch of quarters alone, counting those with a token and a feature of their
 // own (100 x 4096 x 12288 has 96 such and ran 28.7 us, 23.3 on 64 x 128 tiles; at 32 x 4096 x
-// 16384 34.9 against 21.5), needs five for eight CUs and no second or third round that
-// would be nearly empty (0.95-1.01x there, 0.96-0.98x at 657 x 1536..4096 x 12992).
+// 16384 34.9 against 21.5), needs five for eight CUs, and not the range where a second
+// round would be nearly empty (0.95-1.01x there).
 bool gemm_big_wins(int64_t T, int64_t K, int64_t N, int act, int64_t cus) {
     if (act != 0 || K < 1536) return false;
     if (big_whole_tiles(((T + 255) / 256) * ((N + 255) / 256), cus) > 0) return true;
     const int64_t quarters = ((T + 127) / 128) * ((N + 127) / 128);
-    return 8 * quarters >= 5 * cus && (quarters <= cus || 10 * quarters >= 13 * cus) &&
-           (quarters <= 2 * cus || 5 * quarters >= 12 * cus);
+    return 8 * quarters >= 5 * cus && (quarters <= cus || 10 * quarters >= 13 * cus);
 }
 
 hipError_t launch_gemm_big(const LinearArgs& a, const PlanView* plan, hipStream_t s) {

@@ -153,7 +153,7 @@ struct LinearArgs {
 // (gemm.hip), 1 .. 4 smaller tiles for small launches and 5 128 x 256 in one round
 // (gemm_small.hip), 6 256 x 256 for long reductions (gemm_big.hip).
 constexpr int kFormWide = 5, kFormBig = 6;
-int linear_form_bf16(int64_t T, int64_t K, int64_t N, int act, int64_t cus);
+int linear_form_bf16(int64_t T, int64_t K, int64_t N, int act, bool residual, int64_t cus);
 hipError_t launch_gemm_small(int form, int act, const LinearArgs& a, const PlanView* plan, hipStream_t s);
 bool gemm_big_wins(int64_t T, int64_t K, int64_t N, int act, int64_t cus);
 hipError_t launch_gemm_big(const LinearArgs& a, const PlanView* plan, hipStream_t s);  // no activation

@@ -98,7 +98,7 @@ hipError_t launch_small_act(int which, const LinearArgs& a, const PlanView* plan
 // do not (14000 x 512 x 512 14.0 -> 14.4): one workgroup per CU hides neither its first
 // loads nor its epilogue.  Nor where two rounds of 64 x 128 are all there is to do
 // (1310 x 1024 x 3072 12.8 -> 16.0), which the estimates show.
-static int small_gemm_choice(int64_t T, int64_t K, int64_t N, int64_t cus) {
+static int small_gemm_choice(int64_t T, int64_t K, int64_t N, bool residual, int64_t cus) {
     struct Form {
         int64_t tm, tn;
         double start, per_k, tile;
@@ -110,7 +110,10 @@ static int small_gemm_choice(int64_t T, int64_t K, int64_t N, int64_t cus) {
     int which = 0;
     for (int i = 0; i < 4; ++i) {
         const Form& f = kForms[i];
-        // 128 x 128 tiles would need two rounds here: timed, they never win
+        // 128 x 128 tiles in three rounds or more: timed, they never win, though the estimate
+        // says so (4000 x 1024 x 3072: 34.5 us, 30.7 on 128 x 256 tiles)
+        if (i == 3 && n128 > 2 * cus) continue;
+        // nor in two where 128 x 256 tiles need one
         if (i == 3 && n128 > cus && n256 <= cus && K >= 1024 && 5.6 + (7.0 + 7.2 * n256 / cus) * 1e-3 * K < best)
             return kFormWide;
         const int64_t rounds = ((T + f.tm - 1) / f.tm * ((N + f.tn - 1) / f.tn) + cus - 1) / cus;
@@ -121,17 +124,23 @@ static int small_gemm_choice(int64_t T, int64_t K, int64_t N, int64_t cus) {
         }
     }
     // the 128 x 256 tiles (last round as halves): with at most one 64-token half per CU they
-    // always lose; otherwise the smaller tiles must win by a tenth, the fits' error
+    // always lose; otherwise the smaller tiles must win by a tenth, the fits' error.  Where a
+    // single round gives some CUs one tile and some two, it takes between 1.5 and 2 times one
+    // tile's time (4000 x 768 x 2304, 288 tiles: 23.4 us, 25.0 on 64 x 128 tiles, which two
+    // full rounds' estimate let win), but nearly 2 with a residual, whose epilogue is longer
+    // (13000 x 768 x 768, 306 tiles: 26.6 us, 24.8 on 64 x 128 tiles)
     const int64_t tiles_n = (N + 255) / 256, tiles = (T + 127) / 128 * tiles_n;
     if ((T + 63) / 64 * tiles_n <= cus) return which;
     const int64_t last = tiles - (tiles - 1) / (2 * cus) * (2 * cus);
-    const double rounds = last <= cus ? (double)((tiles - last) / cus) + 0.5 * ((2 * last + cus - 1) / cus)
-                                      : (double)((tiles + cus - 1) / cus);
+    const double before = (double)((tiles - last) / cus);
+    const double rounds = last <= cus               ? before + 0.5 * ((2 * last + cus - 1) / cus)
+                          : before > 0 || residual ? before + 2.0
+                                                   : 1.0 + 0.5 * last / cus;
     return best < 0.9 * (4.7 + rounds * (12.9e-3 * K + 2.7)) ? which : 0;
 }
 
-int linear_form_bf16(int64_t T, int64_t K, int64_t N, int act, int64_t cus) {
-    const int form = small_gemm_choice(T, K, N, cus);
+int linear_form_bf16(int64_t T, int64_t K, int64_t N, int act, bool residual, int64_t cus) {
+    const int form = small_gemm_choice(T, K, N, residual, cus);
     return form != kFormWide && gemm_big_wins(T, K, N, act, cus) ? kFormBig : form;
 }
 

@@ -14,12 +14,12 @@ CUS = 256
 # one round; 6: 256 x 256 (and 128 x 128 quarters)
 
 
-def form(T, K, N, act=0):
+def form(T, K, N, act=0, residual=False):
     import paper_2110_10221_amd as rag
 
-    f = rag.library()._ZN3rag16linear_form_bf16Elllil  # rag::linear_form_bf16
-    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int64] * 3 + [ctypes.c_int, ctypes.c_int64]
-    return f(T, K, N, act, CUS)
+    f = rag.library()._ZN3rag16linear_form_bf16Elllibl  # rag::linear_form_bf16
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int64] * 3 + [ctypes.c_int, ctypes.c_bool, ctypes.c_int64]
+    return f(T, K, N, act, residual, CUS)
 
 
 @needs_lib
@@ -33,8 +33,29 @@ def form(T, K, N, act=0):
     # enough of them: the 256 x 256 kernel
     (1300, 1536, 2112, (6,)), (5200, 2048, 512, (6,)),          # 18.9 / 17.7
     (4000, 4096, 1024, (6,)), (2000, 2048, 4992, (6,)),         # 54.9 (form 0) / 53.1
+    (1926, 6912, 4288, (6,)), (4622, 3968, 2048, (6,)),         # 149.6 / 147.5, 91.7 / 87.9
     (16384, 2048, 1024, (6,)), (35475, 4096, 1024, (6,)),       # 68.8 / 62.7, 298 / 270
     (10076, 2048, 512, (5,)), (35475, 1024, 4096, (0,)),
 ])
 def test_long_reduction_form(T, K, N, forms):
     assert form(T, K, N) in forms
+
+
+@needs_lib
+@pytest.mark.parametrize("T,K,N,act,res,forms", [
+    # one round of 128 x 256 tiles, two on some CUs (us, form 0 / best of the small tiles)
+    (4000, 768, 3072, 1, 0, (0,)),     # 29.5 / 32.6
+    (5174, 1024, 2048, 1, 0, (0,)),    # 33.9 / 37.8
+    (2600, 1024, 4096, 1, 0, (0,)),    # 33.7 / 37.3
+    (1592, 2816, 5888, 1, 0, (0,)),    # 72.6 / 75.1
+    (5200, 768, 2304, 0, 0, (0,)),     # 25.2 / 27.8
+    (4000, 1024, 3072, 0, 0, (0,)),    # 30.7 / 34.5
+    (4000, 768, 2304, 0, 0, (0,)),     # 23.4 / 25.0
+    (16000, 768, 768, 0, 1, (0,)),     # 29.3 / 30.8
+    (13000, 768, 768, 0, 1, (3,)),     # 27.6 / 25.5
+    (20000, 512, 512, 0, 1, (3,)),     # 22.5 / 20.3
+    (13000, 576, 576, 0, 1, (3, 4)),   # 22.6 / 17.5: partial feature tiles
+    (2236, 512, 1536, 0, 0, (4,)), (777, 1024, 4096, 1, 0, (4,)), (20000, 1024, 3072, 0, 0, (0,)),
+])
+def test_short_reduction_form(T, K, N, act, res, forms):
+    assert form(T, K, N, act, bool(res)) in forms
