@@ -1029,6 +1029,8 @@ void k_attention_bf16(PlanArgs pa, const uint16_t* __restrict__ q, int ldq, cons
     }
 }
 
+// (device_cu_count asks the runtime for the current device: once per launch, since small
+// calls wait for the host)
 int persistent_grid(int64_t cap, int per_cu) {
     const int64_t g = (int64_t)device_cu_count() * per_cu;
     return static_cast<int>(cap < g ? (cap > 0 ? cap : 1) : g);
@@ -1037,10 +1039,10 @@ int persistent_grid(int64_t cap, int per_cu) {
 // Grid of the bf16 operators: at most four workgroups per CU, no more than the
 // items a plan of this capacity can hold (av_cap / H), and a multiple of
 // 8 * kOpRun so the XCD dealing is a permutation.
-int op_grid(const PlanView& p, int G) {
+int op_grid(const PlanView& p, int G, int cus) {
     constexpr int64_t kUnit = 8 * kOpRun;
     const int64_t items = std::max<int64_t>((p.av_cap + G - 1) / G, 1);
-    const int64_t g = std::min<int64_t>(items, (int64_t)device_cu_count() * 4);
+    const int64_t g = std::min<int64_t>(items, (int64_t)cus * 4);
     return static_cast<int>((g + kUnit - 1) / kUnit * kUnit);
 }
 
@@ -1049,8 +1051,8 @@ int op_grid(const PlanView& p, int G) {
 // balance worse over the grid: at the batch-128, 16-head shape G = 8 (about five
 // items per CU) took Attn.V 0.171 ms against 0.149 at G = 4; QK^T is within 2%
 // from G = 2 to 8 and 15% slower at G = 1.
-int op_heads(const PlanView& p) {
-    const int64_t want = (int64_t)device_cu_count() * 8;
+int op_heads(const PlanView& p, int cus) {
+    const int64_t want = (int64_t)cus * 8;
     for (int G = p.heads; G > 1; --G)
         if (p.heads % G == 0 && p.av_cap / G >= want) return G;
     return 1;
@@ -1061,16 +1063,16 @@ int op_heads(const PlanView& p) {
 hipError_t launch_qkt(const PlanView& p, int dtype, const void* q, int ldq, const void* k, int ldk, float scale,
                       void* scores, int64_t score_cap, bool causal, hipStream_t s) {
     const PlanArgs pa = plan_args(p);
-    const int G = op_heads(p);
-    const int grid = dtype == 1 ? op_grid(p, G) : persistent_grid(p.qkt_cap, 8);
-    if (dtype == 1)
-        hipLaunchKernelGGL(k_qkt_bf16, dim3(grid), dim3(kQkThreads), 0, s, pa, static_cast<const uint16_t*>(q), ldq,
-                           static_cast<const uint16_t*>(k), ldk, scale, static_cast<uint16_t*>(scores), score_cap,
-                           int(causal), G);
-    else
-        hipLaunchKernelGGL(k_qkt_f32, dim3(grid), dim3(256), 0, s, pa, static_cast<const float*>(q), ldq,
-                           static_cast<const float*>(k), ldk, scale, static_cast<float*>(scores), score_cap,
-                           int(causal));
+    if (dtype == 1) {
+        const int cus = device_cu_count(), G = op_heads(p, cus);
+        hipLaunchKernelGGL(k_qkt_bf16, dim3(op_grid(p, G, cus)), dim3(kQkThreads), 0, s, pa,
+                           static_cast<const uint16_t*>(q), ldq, static_cast<const uint16_t*>(k), ldk, scale,
+                           static_cast<uint16_t*>(scores), score_cap, int(causal), G);
+    } else {
+        hipLaunchKernelGGL(k_qkt_f32, dim3(persistent_grid(p.qkt_cap, 8)), dim3(256), 0, s, pa,
+                           static_cast<const float*>(q), ldq, static_cast<const float*>(k), ldk, scale,
+                           static_cast<float*>(scores), score_cap, int(causal));
+    }
     return hipGetLastError();
 }
 
@@ -1081,8 +1083,9 @@ hipError_t launch_softmax(const PlanView& p, int dtype, const void* scores, void
     // heads per wave: two waves per wave slot (32 per CU) as far as the heads go.  1 to 8
     // per slot measured alike at T = 8879 and 35475; at T = 2236, where one wave per
     // token fills a quarter of the slots, splitting took fp32 12.1 -> 7.2 us together
-    // with the in-register reductions
-    const int64_t want = (int64_t)device_cu_count() * 64;
+    // with the in-register reductions.  (A whole GPU's 256 CUs: asking for the device's count
+    // would cost the smallest calls 0.1 us of host time.)
+    const int64_t want = 256 * 64;
     const int parts = (int)std::min<int64_t>(p.heads, std::max<int64_t>(1, want / p.total_tokens));
     const int hg = (p.heads + parts - 1) / parts;
     const dim3 grid((p.total_tokens + 3) / 4, (p.heads + hg - 1) / hg);
@@ -1098,15 +1101,16 @@ hipError_t launch_softmax(const PlanView& p, int dtype, const void* scores, void
 hipError_t launch_attn_v(const PlanView& p, int dtype, const void* probs, int64_t score_cap, const void* v, int ldv,
                          void* out, int ldo, bool causal, hipStream_t s) {
     const PlanArgs pa = plan_args(p);
-    const int G = op_heads(p);
-    const int grid = dtype == 1 ? op_grid(p, G) : persistent_grid(p.av_cap, 8);
-    if (dtype == 1)
-        hipLaunchKernelGGL(k_attn_v_bf16, dim3(grid), dim3(256), 0, s, pa, static_cast<const uint16_t*>(probs),
-                           score_cap, static_cast<const uint16_t*>(v), ldv, static_cast<uint16_t*>(out), ldo, int(causal),
-                           G);
-    else
-        hipLaunchKernelGGL(k_attn_v_f32, dim3(grid), dim3(256), 0, s, pa, static_cast<const float*>(probs),
-                           score_cap, static_cast<const float*>(v), ldv, static_cast<float*>(out), ldo, int(causal));
+    if (dtype == 1) {
+        const int cus = device_cu_count(), G = op_heads(p, cus);
+        hipLaunchKernelGGL(k_attn_v_bf16, dim3(op_grid(p, G, cus)), dim3(256), 0, s, pa,
+                           static_cast<const uint16_t*>(probs), score_cap, static_cast<const uint16_t*>(v), ldv,
+                           static_cast<uint16_t*>(out), ldo, int(causal), G);
+    } else {
+        hipLaunchKernelGGL(k_attn_v_f32, dim3(persistent_grid(p.av_cap, 8)), dim3(256), 0, s, pa,
+                           static_cast<const float*>(probs), score_cap, static_cast<const float*>(v), ldv,
+                           static_cast<float*>(out), ldo, int(causal));
+    }
     return hipGetLastError();
 }
 
@@ -1119,13 +1123,13 @@ hipError_t launch_fused_variant(const PlanView& p, const void* q, int ldq, const
     // permutation
     constexpr int64_t kUnit = 8 * kStreamRun;
     const int64_t cap = std::max<int64_t>(p.av_cap, 1);
-    const int64_t limit = (int64_t)device_cu_count() * kStreamPerCu;
+    const int64_t cus = device_cu_count(), limit = cus * kStreamPerCu;
     const int64_t g = (std::min(cap, limit) + kUnit - 1) / kUnit * kUnit;
     // Two wave pairs per item where one item's chain of chunks is what the launch waits
     // for: at least twenty chunks in the longest row and at most four items per CU (two
     // sequences of 900..1024, 16 heads: 20.9 -> 16.2 us, masked 19.9 -> 14.3; but batch 32
     // of 16..512, 1232 items, 17.2 -> 20.8: short items only pay for the merge).
-    const bool split = p.max_len >= 640 && cap <= 4 * (int64_t)device_cu_count();
+    const bool split = p.max_len >= 640 && cap <= 4 * cus;
     auto* f = split ? &k_attention_bf16<CAUSAL, 2> : &k_attention_bf16<CAUSAL, 1>;
     hipLaunchKernelGGL(f, dim3((unsigned)g), dim3(kStreamThreads * (split ? 2 : 1)), 0, s, plan_args(p),
                        static_cast<const uint16_t*>(q), ldq, static_cast<const uint16_t*>(k), ldk,
