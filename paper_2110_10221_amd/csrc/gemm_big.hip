@@ -237,16 +237,23 @@ static int64_t big_whole_tiles(int64_t tiles, int64_t cus) {
 
 // Long reductions only (sixteen 64-k steps barely pay for the exposed epilogue: of 162
 // timed shapes, T = 2236 to 35475, those with K >= 1536 ran 1-12% faster than on the other
-// tiles and nearly all shorter ones slower), without an activation, and with enough for the
-// CUs to do.  A launch of quarters alone, counting those with a token and a feature of their
-// own (100 x 4096 x 12288 has 96 such and ran 28.7 us, 23.3 on 64 x 128 tiles; at 32 x 4096 x
-// 16384 34.9 against 21.5), needs five for eight CUs, and not the range where a second
-// round would be nearly empty (0.95-1.01x there).
-bool gemm_big_wins(int64_t T, int64_t K, int64_t N, int act, int64_t cus) {
+// tiles and nearly all shorter ones slower), without an activation.
+//  - A second round of whole tiles, or part of one, only where the 128 x 256 tiles, which
+//    pad the tokens less, need one too (2580 x 2048 x 6144: 66.5 us, 59.1 on 504 of them).
+//  - A launch of quarters alone not where 64 x 128 tiles make one round (100 x 4096 x 12288
+//    28.7 us, 23.3 on those; 32 x 4096 x 16384 34.9 and 21.5; but 2236 x 4096 x 1024 28.0, and
+//    30.9 on 128 x 128 tiles), nor with a nearly empty second round (0.95-1.01x
+//    there), which empty quarters cause too: they go to the XCDs in turn with the others, and
+//    33 full ones on one XCD take two rounds (2580 x 6144 x 1536, 252 of 264 full: 84 us, 52
+//    on 128 x 128 tiles).  In more than one round without a residual, whose epilogue the other
+//    tiles are slow at, it takes K >= 2048 (2442 x 1536 x 4608: 42.1 us, 39.5 on the others).
+bool gemm_big_wins(int64_t T, int64_t K, int64_t N, int act, bool residual, int64_t cus) {
     if (act != 0 || K < 1536) return false;
-    if (big_whole_tiles(((T + 255) / 256) * ((N + 255) / 256), cus) > 0) return true;
-    const int64_t quarters = ((T + 127) / 128) * ((N + 127) / 128);
-    return 8 * quarters >= 5 * cus && (quarters <= cus || 10 * quarters >= 13 * cus);
+    const int64_t tiles = ((T + 255) / 256) * ((N + 255) / 256), halves = ((T + 127) / 128) * ((N + 255) / 256);
+    if (big_whole_tiles(tiles, cus) > 0) return tiles <= cus || halves > 2 * cus;
+    if (((T + 63) / 64) * ((N + 127) / 128) <= cus) return false;
+    const int64_t full = ((T + 127) / 128) * ((N + 127) / 128);  // of 4 * tiles quarters
+    return 4 * tiles <= cus || (10 * full >= 13 * cus && (residual || K >= 2048));
 }
 
 hipError_t launch_gemm_big(const LinearArgs& a, const PlanView* plan, hipStream_t s) {

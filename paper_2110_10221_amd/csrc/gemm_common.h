@@ -155,7 +155,7 @@ struct LinearArgs {
 constexpr int kFormWide = 5, kFormBig = 6;
 int linear_form_bf16(int64_t T, int64_t K, int64_t N, int act, bool residual, int64_t cus);
 hipError_t launch_gemm_small(int form, int act, const LinearArgs& a, const PlanView* plan, hipStream_t s);
-bool gemm_big_wins(int64_t T, int64_t K, int64_t N, int act, int64_t cus);
+bool gemm_big_wins(int64_t T, int64_t K, int64_t N, int act, bool residual, int64_t cus);
 hipError_t launch_gemm_big(const LinearArgs& a, const PlanView* plan, hipStream_t s);  // no activation
 
 // Grid of a vgemm launch over `entries` list entries at most, `parts` workgroups each, dealt

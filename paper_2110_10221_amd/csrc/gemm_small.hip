@@ -141,7 +141,7 @@ static int small_gemm_choice(int64_t T, int64_t K, int64_t N, bool residual, int
 
 int linear_form_bf16(int64_t T, int64_t K, int64_t N, int act, bool residual, int64_t cus) {
     const int form = small_gemm_choice(T, K, N, residual, cus);
-    return form != kFormWide && gemm_big_wins(T, K, N, act, cus) ? kFormBig : form;
+    return form != kFormWide && gemm_big_wins(T, K, N, act, residual, cus) ? kFormBig : form;
 }
 
 hipError_t launch_gemm_small(int form, int act, const LinearArgs& a, const PlanView* plan, hipStream_t s) {

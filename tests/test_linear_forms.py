@@ -23,22 +23,31 @@ def form(T, K, N, act=0, residual=False):
 
 
 @needs_lib
-@pytest.mark.parametrize("T,K,N,forms", [
+@pytest.mark.parametrize("T,K,N,res,forms", [
     # few tokens: most of a 128-row quarter is empty (us, best of the small tiles / 256 x 256)
-    (1, 4224, 14272, (1, 2)),      # 18.7 / 26.5
-    (8, 3968, 13760, (1, 2)),      # 17.6 / 25.1
-    (32, 4096, 16384, (1, 2)),     # 21.5 / 34.9
-    (100, 4096, 12288, (2, 3)),    # 23.3 / 28.7
-    (257, 4096, 5120, (2, 3)),     # 21.9 / 29.2
+    (1, 4224, 14272, 0, (1, 2)),      # 18.7 / 26.5
+    (8, 3968, 13760, 0, (1, 2)),      # 17.6 / 25.1
+    (32, 4096, 16384, 0, (1, 2)),     # 21.5 / 34.9
+    (100, 4096, 12288, 0, (2, 3)),    # 23.3 / 28.7
+    (257, 4096, 5120, 0, (2, 3)),     # 21.9 / 29.2
+    (897, 4032, 2112, 1, (3,)),       # 22.7 / 26.2
     # enough of them: the 256 x 256 kernel
-    (1300, 1536, 2112, (6,)), (5200, 2048, 512, (6,)),          # 18.9 / 17.7
-    (4000, 4096, 1024, (6,)), (2000, 2048, 4992, (6,)),         # 54.9 (form 0) / 53.1
-    (1926, 6912, 4288, (6,)), (4622, 3968, 2048, (6,)),         # 149.6 / 147.5, 91.7 / 87.9
-    (16384, 2048, 1024, (6,)), (35475, 4096, 1024, (6,)),       # 68.8 / 62.7, 298 / 270
-    (10076, 2048, 512, (5,)), (35475, 1024, 4096, (0,)),
+    (1300, 1536, 2112, 0, (6,)), (5200, 2048, 512, 0, (6,)),          # 18.9 / 17.7
+    (4000, 4096, 1024, 0, (6,)), (2000, 2048, 4992, 0, (6,)),         # 54.9 (form 0) / 53.1
+    (1926, 6912, 4288, 0, (6,)), (4622, 3968, 2048, 0, (6,)),         # 149.6 / 147.5, 91.7 / 87.9
+    (16384, 2048, 1024, 0, (6,)), (35475, 4096, 1024, 0, (6,)),       # 68.8 / 62.7, 298 / 270
+    (10076, 2048, 512, 0, (5,)), (35475, 1024, 4096, 0, (0,)),
+    # (2580 tokens: the last 256-token row of tiles is a twelfth full)
+    (2580, 6144, 1536, 1, (4,)),      # 52.4 / 84.0
+    (2580, 1536, 1536, 1, (4,)),      # 16.0 / 24.7
+    (2580, 2048, 6144, 0, (0,)),      # 59.1 / 68.8
+    (2236, 4096, 1024, 1, (6,)), (4980, 5440, 448, 0, (6,)),    # 30.9 / 28.0, 37.6 / 33.7
+    (2700, 2048, 6144, 0, (6,)), (2580, 1536, 4608, 0, (6,)),   # 76 / 66, 39.0 / 38.6
+    (2442, 1536, 4608, 0, (0,)),      # 39.5 / 42.0
+    (6000, 1536, 1536, 1, (6,)),      # 40.7 / 39.4
 ])
-def test_long_reduction_form(T, K, N, forms):
-    assert form(T, K, N) in forms
+def test_long_reduction_form(T, K, N, res, forms):
+    assert form(T, K, N, 0, bool(res)) in forms
 
 
 @needs_lib
