@@ -790,7 +790,7 @@ hipError_t launch_linear(int dtype, const void* x, int ldx, const void* w, const
             const LinearArgs a{static_cast<const uint16_t*>(x), ldx, static_cast<const uint16_t*>(w),
                                static_cast<const uint16_t*>(bias), static_cast<const uint16_t*>(residual), ldr,
                                static_cast<uint16_t*>(y), ldy, T, K, N};
-            const int form = linear_form_bf16(T, K, N, act, residual != nullptr, device_cu_count());
+            const int form = linear_form_bf16(T, K, N, act, residual != nullptr, plan ? plan->batch : 0, device_cu_count());
             if (form == kFormBig) return launch_gemm_big(a, plan, s);
             if (form != 0) return launch_gemm_small(form, act, a, plan, s);
         }

@@ -149,11 +149,12 @@ struct LinearArgs {
     int ldy, T, K, N;
 };
 
-// The tile form a bf16 packed linear call runs, by its sizes: 0 the 128 x 256 tiles
+// The tile form a bf16 packed linear call runs, by its sizes and the sequences of the plan it
+// carries (0 without one): 0 the 128 x 256 tiles
 // (gemm.hip), 1 .. 4 smaller tiles for small launches and 5 128 x 256 in one round
 // (gemm_small.hip), 6 256 x 256 for long reductions (gemm_big.hip).
 constexpr int kFormWide = 5, kFormBig = 6;
-int linear_form_bf16(int64_t T, int64_t K, int64_t N, int act, bool residual, int64_t cus);
+int linear_form_bf16(int64_t T, int64_t K, int64_t N, int act, bool residual, int64_t plan_batch, int64_t cus);
 hipError_t launch_gemm_small(int form, int act, const LinearArgs& a, const PlanView* plan, hipStream_t s);
 bool gemm_big_wins(int64_t T, int64_t K, int64_t N, int act, bool residual, int64_t cus);
 hipError_t launch_gemm_big(const LinearArgs& a, const PlanView* plan, hipStream_t s);  // no activation

@@ -139,9 +139,21 @@ static int small_gemm_choice(int64_t T, int64_t K, int64_t N, bool residual, int
     return best < 0.9 * (4.7 + rounds * (12.9e-3 * K + 2.7)) ? which : 0;
 }
 
-int linear_form_bf16(int64_t T, int64_t K, int64_t N, int act, bool residual, int64_t cus) {
-    const int form = small_gemm_choice(T, K, N, residual, cus);
-    return form != kFormWide && gemm_big_wins(T, K, N, act, residual, cus) ? kFormBig : form;
+// The workgroups of a plan that rides along (plan_batch) ask for as much LDS as the tiles. On
+// the forms with one workgroup per CU they wait for the CUs the tiles leave free, or for the
+// tiles: a layer of 40 sequences, T = 2454, d = 1024, took 119.1 us (113.1 with its plan built
+// before) and 114.5 on 128 x 256 tiles, two per CU; d = 512 64.3 (58.3) and 59.4, with 128
+// sequences 67.2 and 60.4.  (Past K = 1024 these forms gain more than the 6 to 12 us.)
+static bool plan_waits(int form, int64_t T, int64_t K, int64_t N, int64_t plan_batch, int64_t cus) {
+    if ((form != 4 && form != kFormWide) || K > 1024) return false;
+    const int64_t tiles = (T + 127) / 128 * (form == kFormWide ? (N + 255) / 256 : (N + 127) / 128);
+    return plan_batch > (cus - tiles % cus) % cus;
+}
+
+int linear_form_bf16(int64_t T, int64_t K, int64_t N, int act, bool residual, int64_t plan_batch, int64_t cus) {
+    int form = small_gemm_choice(T, K, N, residual, cus);
+    if (form != kFormWide && gemm_big_wins(T, K, N, act, residual, cus)) form = kFormBig;
+    return plan_waits(form, T, K, N, plan_batch, cus) ? 0 : form;
 }
 
 hipError_t launch_gemm_small(int form, int act, const LinearArgs& a, const PlanView* plan, hipStream_t s) {

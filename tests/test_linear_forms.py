@@ -14,12 +14,13 @@ CUS = 256
 # one round; 6: 256 x 256 (and 128 x 128 quarters)
 
 
-def form(T, K, N, act=0, residual=False):
+def form(T, K, N, act=0, residual=False, plan_batch=0):
     import paper_2110_10221_amd as rag
 
-    f = rag.library()._ZN3rag16linear_form_bf16Elllibl  # rag::linear_form_bf16
-    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int64] * 3 + [ctypes.c_int, ctypes.c_bool, ctypes.c_int64]
-    return f(T, K, N, act, residual, CUS)
+    f = rag.library()._ZN3rag16linear_form_bf16Elllibll  # rag::linear_form_bf16
+    f.restype = ctypes.c_int
+    f.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int, ctypes.c_bool, ctypes.c_int64, ctypes.c_int64]
+    return f(T, K, N, act, residual, plan_batch, CUS)
 
 
 @needs_lib
@@ -68,3 +69,20 @@ def test_long_reduction_form(T, K, N, res, forms):
 ])
 def test_short_reduction_form(T, K, N, act, res, forms):
     assert form(T, K, N, act, bool(res)) in forms
+
+
+@needs_lib
+@pytest.mark.parametrize("T,d,batch,forms", [
+    # QKV projections: the form without a plan, and with one of `batch` sequences
+    (2454, 512, 40, (4, 0)),     # the layer: 64.3 us with form 4, 59.4
+    (2580, 512, 128, (4, 0)),    # 67.2, 60.4
+    (2442, 512, 16, (4, 4)),     # 16 CUs are free: 59.3, 60.4
+    (2236, 512, 32, (4, 4)),     # 40 are
+    (2454, 1024, 40, (5, 0)),    # 119.1, 114.5
+    (2442, 1024, 16, (5, 5)),    # 113.4, 115.8
+    (507, 512, 8, (2, 2)),       # 32.5, 36.6: two workgroups per CU
+    (1000, 2048, 40, (5, 5)),    # the projection alone: 28.8, 39.5
+    (507, 1536, 8, (6, 6)),      # 72.7, 83.9
+])
+def test_form_leaves_the_plan_room(T, d, batch, forms):
+    assert (form(T, d, 3 * d), form(T, d, 3 * d, plan_batch=batch)) == forms
