@@ -433,17 +433,19 @@ __global__ __launch_bounds__(256) void k_softmax(PlanArgs pa, const typename Row
     const int h0 = blockIdx.y * hg, h1 = min(H, h0 + hg);
     constexpr int E = IO::kPer;
     if (L < E) {
-        // eight lanes per row, one value each
-        const int e = lane % 8;
-        for (int h = h0 + lane / 8; h - lane / 8 < h1; h += kWave / 8) {
+        // E lanes per row, one value each
+        const int e = lane % E;
+        for (int h = h0 + lane / E; h - lane / E < h1; h += kWave / E) {
             const bool valid = h < h1 && e < L;
             const int64_t off = row0 + (int64_t)h * ld + e;
             const float x = valid ? IO::load1(S + off) : -FLT_MAX;
-            const float m = group_max<8>(x);  // (all lanes take part)
+            const float m = group_max<E>(x);  // (all lanes take part)
             const float ex = valid ? IO::exp(x - m) : 0.f;
-            const float inv = 1.0f / group_sum<8>(ex);
+            const float inv = 1.0f / group_sum<E>(ex);
             if (valid) IO::store1(P + off, ex * inv);
         }
+    } else if (L <= 2 * E) {
+        softmax_rows<BF16, 2, 1>(S, P, row0, ld, L, h0, h1, lane);
     } else if (L <= 8 * E) {
         softmax_rows<BF16, 8, 1>(S, P, row0, ld, L, h0, h1, lane);
     } else if (L <= 16 * E) {
@@ -1084,10 +1086,12 @@ hipError_t launch_softmax(const PlanView& p, int dtype, const void* scores, void
     // per slot measured alike at T = 8879 and 35475; at T = 2236, where one wave per
     // token fills a quarter of the slots, splitting took fp32 12.1 -> 7.2 us together
     // with the in-register reductions.  (A whole GPU's 256 CUs: asking for the device's count
-    // would cost the smallest calls 0.1 us of host time.)
+    // would cost the smallest calls 0.1 us of host time.)  A wave takes at least the heads it
+    // does at once on rows of 32 scores or fewer: 1000 sequences of 1..10, 4 heads, 3.9 us in
+    // fp32, 4.8 split in two.
     const int64_t want = 256 * 64;
-    const int parts = (int)std::min<int64_t>(p.heads, std::max<int64_t>(1, want / p.total_tokens));
-    const int hg = (p.heads + parts - 1) / parts;
+    const int64_t parts = std::min<int64_t>(p.heads, std::max<int64_t>(1, want / p.total_tokens));
+    const int hg = (int)std::max<int64_t>((p.heads + parts - 1) / parts, p.max_len <= 32 ? 8 : 1);
     const dim3 grid((p.total_tokens + 3) / 4, (p.heads + hg - 1) / hg);
     if (dtype == 1)
         hipLaunchKernelGGL(k_softmax<true>, grid, dim3(256), 0, s, pa, static_cast<const uint16_t*>(scores),
