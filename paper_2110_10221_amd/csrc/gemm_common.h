@@ -173,6 +173,10 @@ inline VgemmGrid vgemm_grid(int64_t entries, int64_t parts, int64_t run, int64_t
     return all <= most ? VgemmGrid{(int)all, false} : VgemmGrid{(int)most, true};
 }
 
+// The tiles of an fp32 packed linear call: 128 (128 x 128; only if 32-bit offsets reach 128
+// rows of x and w: leading dimensions below 2^22) or 64 (64 x 64), plus one if the last round
+// of tiles runs as quarters.
+int linear_form_f32(int64_t T, int64_t N, bool reach128, int64_t cus);
 // fp32 launchers (gemm_f32.hip), called by the launchers that take both types.
 hipError_t launch_linear_f32(const float* x, int ldx, const float* w, const float* bias, const float* residual, int ldr,
                              int act, float* y, int ldy, int T, int K, int N, hipStream_t s);

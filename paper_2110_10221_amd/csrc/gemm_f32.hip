@@ -418,27 +418,15 @@ hipError_t launch_f32(const float* x, int ldx, const float* w, const float* bias
     return hipGetLastError();
 }
 
-// Tiles and whether their last round runs as quarters: whichever gives the busiest CU
-// the least work, in units of one 64 x 64 tile and rounds of one tile per CU.  A
-// 128 x 128 tile re-reads its operands half as often (weight 4 against 4.2 for
-// four 64 x 64) and a 32 x 32 quarter twice as often (0.31 against 0.25).
 template <int ACT, bool WIDE>
 hipError_t launch_f32_tiles(const float* x, int ldx, const float* w, const float* bias, const float* residual, int ldr,
                             float* y, int ldy, int T, int K, int N, hipStream_t s) {
-    const int64_t cus = device_cu_count();
-    auto cost = [&](int64_t side, double tile, double quarter, bool& split) {
-        const int64_t tiles = ((T + side - 1) / side) * ((N + side - 1) / side);
-        const int64_t full = tiles / cus, rest = tiles % cus;
-        const double q = ((4 * rest + cus - 1) / cus) * quarter;
-        split = rest && q < tile;
-        return full * tile + (rest ? (split ? q : tile) : 0.0);
-    };
-    bool split_big, split_mid;
-    const double big = cost(128, 4.0, 1.05, split_big), mid = cost(64, 1.05, 0.31, split_mid);
-    // (leading dimensions between 2^22 and 2^23 reach 64 rows, but not 128)
-    if (big <= mid && f32_reach(std::min(T, 128), ldx, K) && f32_reach(std::min(N, 128), K, K))
-        return launch_f32<F32Big, F32Mid, ACT, WIDE>(x, ldx, w, bias, residual, ldr, y, ldy, T, K, N, split_big, s);
-    return launch_f32<F32Mid, F32Tiny, ACT, WIDE>(x, ldx, w, bias, residual, ldr, y, ldy, T, K, N, split_mid, s);
+    const bool reach = f32_reach(std::min(T, 128), ldx, K) && f32_reach(std::min(N, 128), K, K);
+    const int form = linear_form_f32(T, N, reach, device_cu_count());
+    const bool split = (form & 1) != 0;
+    if (form & 128)
+        return launch_f32<F32Big, F32Mid, ACT, WIDE>(x, ldx, w, bias, residual, ldr, y, ldy, T, K, N, split, s);
+    return launch_f32<F32Mid, F32Tiny, ACT, WIDE>(x, ldx, w, bias, residual, ldr, y, ldy, T, K, N, split, s);
 }
 
 template <int ACT>
@@ -553,6 +541,26 @@ hipError_t launch_trmm_tiles(const float* l, int ldl, const float* b, int ldb, f
 }
 
 }  // namespace
+
+// Tiles and whether their last round runs as quarters: whichever gives the busiest CU
+// the least work, in units of one 64 x 64 tile and rounds of one tile per CU.  A
+// 128 x 128 tile re-reads its operands half as often (weight 4 against 4.2 for
+// four 64 x 64) and a 32 x 32 quarter twice as often (0.31 against 0.25).  128 x 128 tiles
+// that would all run as quarters are 64 x 64 tiles with registers and LDS for more (3000 x 1024
+// x 1024: 56.7 us, 54.1 as those; 710 x 128 x 4076 13.5, 12.0).
+int linear_form_f32(int64_t T, int64_t N, bool reach128, int64_t cus) {
+    auto cost = [&](int64_t side, double tile, double quarter, bool& split, bool& whole) {
+        const int64_t tiles = ((T + side - 1) / side) * ((N + side - 1) / side);
+        const int64_t full = tiles / cus, rest = tiles % cus;
+        const double q = ((4 * rest + cus - 1) / cus) * quarter;
+        split = rest && q < tile;
+        whole = full > 0 || !split;
+        return full * tile + (rest ? (split ? q : tile) : 0.0);
+    };
+    bool split_big, split_mid, whole_big, whole_mid;
+    const double big = cost(128, 4.0, 1.05, split_big, whole_big), mid = cost(64, 1.05, 0.31, split_mid, whole_mid);
+    return reach128 && whole_big && big <= mid ? 128 + split_big : 64 + split_mid;
+}
 
 hipError_t launch_linear_f32(const float* x, int ldx, const float* w, const float* bias, const float* residual, int ldr,
                              int act, float* y, int ldy, int T, int K, int N, hipStream_t s) {

@@ -1,5 +1,5 @@
-"""The tile form a bf16 packed linear call takes (host arithmetic, no GPU needed), at
-sizes where every form was timed: the rule must not name one measured slower."""
+"""The tile form a packed linear call takes (host arithmetic, no GPU needed), at sizes where
+every form was timed: the rule must not name one measured slower."""
 import ctypes
 import os
 
@@ -86,3 +86,19 @@ def test_short_reduction_form(T, K, N, act, res, forms):
 ])
 def test_form_leaves_the_plan_room(T, d, batch, forms):
     assert (form(T, d, 3 * d), form(T, d, 3 * d, plan_batch=batch)) == forms
+
+
+@needs_lib
+@pytest.mark.parametrize("T,N,expected", [
+    (500, 4096, 64), (3000, 1024, 64),   # quarters of 128 x 128 tiles: 38.5 (38.6), 56.7 (54.1) us
+    (777, 2304, 64), (2300, 520, 65),
+    (4300, 1030, 129),            # 306 tiles of 128 x 128, the last 50 as quarters
+    (5000, 1024, 129), (4096, 2048, 128), (10076, 512, 129), (1, 4096, 65),
+])
+def test_f32_form(T, N, expected):
+    import paper_2110_10221_amd as rag
+
+    f = rag.library()._ZN3rag15linear_form_f32Ellbl  # rag::linear_form_f32
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int64, ctypes.c_int64, ctypes.c_bool, ctypes.c_int64]
+    assert f(T, N, True, CUS) == expected
+    assert f(T, N, False, CUS) in (64, 65)
