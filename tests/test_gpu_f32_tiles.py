@@ -13,15 +13,30 @@ from workloads import make_trmm_operands, make_vgemm_operands, random_storage
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("T,K,N,pad,shift", [
-    (1, 1, 1, 0, 0), (1, 1, 1, 2, 1),                      # one element
-    (33, 31, 65, 0, 0), (64, 4, 64, 4, 0), (65, 36, 130, 3, 1),   # k below, at and past one 32-k step
-    (63, 32, 31, 0, 0), (64, 64, 64, 1, 1), (97, 100, 33, 4, 4),  # 16-byte aligned rows (pad, shift % 4 == 0) and not
-    (2300, 100, 520, 0, 0), (2300, 101, 519, 0, 0),       # 333 tiles of 64 x 64: a last round of quarters
-    (8200, 68, 520, 0, 0),                                # 325 tiles of 128 x 128: quarters of 64 x 64
-    (4100, 33, 1030, 1, 1),
+def _form(T, N):
+    """The tiles of an fp32 linear call (see rag::linear_form_f32): 128 or 64, plus one where
+    the last round runs as quarters."""
+    import ctypes
+
+    import paper_2110_10221_amd as rag
+
+    f = rag.library()._ZN3rag15linear_form_f32Ellbl
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int64, ctypes.c_int64, ctypes.c_bool, ctypes.c_int64]
+    return f(T, N, True, torch.cuda.get_device_properties(0).multi_processor_count)
+
+
+@pytest.mark.parametrize("T,K,N,pad,shift,form", [
+    (1, 1, 1, 0, 0, 65), (1, 1, 1, 2, 1, 65),                         # one element
+    (33, 31, 65, 0, 0, 65), (64, 4, 64, 4, 0, 65), (65, 36, 130, 3, 1, 65),  # k below, at and past one 32-k step
+    (63, 32, 31, 0, 0, 65), (64, 64, 64, 1, 1, 65), (97, 100, 33, 4, 4, 65),  # 16-byte aligned rows (pad, shift % 4 == 0) and not
+    (2300, 100, 520, 0, 0, 65), (2300, 101, 519, 0, 0, 65),           # 324 tiles of 64 x 64, 68 as quarters
+    (8200, 68, 520, 0, 0, 65), (4100, 33, 1030, 1, 1, 65),            # four rounds of them, then quarters
+    (4300, 68, 1030, 0, 0, 129), (4300, 33, 1030, 1, 1, 129),         # 306 tiles of 128 x 128, 50 as quarters of 64 x 64
+    (16300, 36, 250, 4, 0, 128), (16300, 35, 250, 0, 0, 128),         # one round of 128 x 128 tiles
+    (3000, 36, 1000, 0, 0, 64),                                       # whole 64 x 64 tiles alone
 ])
-def test_linear_any_shape(T, K, N, pad, shift):
+def test_linear_any_shape(T, K, N, pad, shift, form):
+    assert _form(T, N) == form
     import paper_2110_10221_amd as rag
 
     rng = np.random.default_rng(T + 7 * K + N)

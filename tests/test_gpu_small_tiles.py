@@ -45,7 +45,8 @@ def test_small_tiles(T, K, N, act, res):
 
 
 @pytest.mark.parametrize("lengths,heads", [([5, 70, 33], 2), ([64] * 40 + [3] * 100, 4), ([17] * 256, 8),
-                                           ([200, 1, 300] * 5, 8), ([64] * 23 + [30], 16)])
+                                           ([200, 1, 300] * 5, 8), ([64] * 23 + [30], 16), ([40] * 13, 24),
+                                           ([100] * 8, 6), ([50] * 10, 12)])
 def test_layer_builds_its_plan_in_a_small_launch(lengths, heads):
     # the plan's workgroups behind each tile form: bit-identical to a plan built ahead
     import paper_2110_10221_amd as rag

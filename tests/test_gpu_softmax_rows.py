@@ -25,7 +25,8 @@ def _plan(L, H):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("L,H", [(EDGES[:20], 3), (EDGES[20:], 1), ([9, 40, 100, 200, 300, 600], 17), ([8] * 7, 2), ([1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 32], 19),
+@pytest.mark.parametrize("L,H", [(EDGES[:20], 3), (EDGES[20:], 1), ([9, 40, 100, 200, 300, 600], 17), ([8] * 7, 2),
+                                 ([1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 32], 19),
                                  ([130] * 140, 5)])
 @pytest.mark.parametrize("shift", [0, 1])
 def test_row_forms(dtype, L, H, shift):

@@ -89,6 +89,23 @@ def test_form_leaves_the_plan_room(T, d, batch, forms):
 
 
 @needs_lib
+@pytest.mark.parametrize("expected,shapes", [
+    (1, [(1, 64, 64), (31, 128, 64), (33, 192, 192), (100, 64, 64), (300, 320, 320)]),
+    (2, [(1000, 512, 512), (777, 64, 1088), (1501, 256, 320), (2500, 320, 1600)]),
+    (3, [(900, 192, 1600), (1700, 448, 832), (2236, 2048, 512)]),
+    (4, [(1300, 64, 2112), (3000, 192, 1088), (2236, 512, 1536)]),
+    (5, [(4300, 1024, 960), (2000, 1088, 4032), (10241, 1216, 448)]),
+    (6, [(1300, 1536, 2112), (8300, 1600, 2112), (16384, 2048, 1024), (16129, 1536, 960)]),
+])
+def test_parity_shapes_reach_their_form(expected, shapes):
+    # the shapes by which the GPU tests cover each form
+    for s in shapes:
+        assert form(*s, 0, True) == expected, s
+        if expected < 6:
+            assert form(*s, 1) == expected, s
+
+
+@needs_lib
 @pytest.mark.parametrize("T,N,expected", [
     (500, 4096, 64), (3000, 1024, 64),   # quarters of 128 x 128 tiles: 38.5 (38.6), 56.7 (54.1) us
     (777, 2304, 64), (2300, 520, 65),
