@@ -53,22 +53,9 @@ __device__ __forceinline__ bool plan_ok(const PlanArgs& pa, int64_t score_cap) {
 
 __device__ __forceinline__ u32x4 ld16(const uint16_t* p) { return *reinterpret_cast<const u32x4*>(p); }
 
-// The status word is written in these kernels (atomicOr), so the compiler cannot
-// keep plan reads in scalar registers by itself; values that are uniform over the
-// workgroup are made so explicitly (a buffer descriptor built from a per-lane value
-// becomes a loop over lanes).
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ int64_t uni64(int64_t v) {
-    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
-    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(static_cast<uint64_t>(v) >> 32));
-    return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
-}
-
 // ---------------------------------------------------------------------------
 // QK^T
 // ---------------------------------------------------------------------------
-
-typedef __attribute__((address_space(3))) void lds_void_t;
 
 // Element offset of (row, col) in [rows][64 channels] LDS storage (128-byte rows,
 // two per 256-byte bank line) whose 16-byte chunks are XOR-swizzled by row bits
@@ -119,13 +106,13 @@ __device__ __forceinline__ int op_item(int bid, int grid) {  // grid: a multiple
 }
 
 // bf16 QK^T.  Per head of the item and piece of kPiece keys, wave w computes the
-// piece's key tile w for all 64 query rows of the block (v_mfma_f32_16x16x32_bf16,
+// piece's w-th 32 keys for all 64 query rows of the block (v_mfma_f32_16x16x32_bf16,
 // K fragments straight from memory, the next piece's tile loaded while this one
 // is computed), scaled and rounded into the workgroup's LDS rows; then all
-// threads write the piece's row pieces as aligned 16-byte chunks (a row starts at
-// any element, so a chunk is cut from two LDS chunks by a funnel shift), and
-// 2-byte stores for the partial chunks at both ends of each row piece.
-constexpr int kPiece = 4 * kTile;         // keys per written row piece: one tile per wave
+// threads write the piece's row pieces as 16-byte chunks at the row's own element
+// offset (any alignment), and the up to seven elements past the last chunk as
+// 2-byte stores.
+constexpr int kPiece = 4 * kTile;         // keys per written row piece
 constexpr int kPieceRow = kPiece + 8;     // LDS row (elements): 16-byte aligned, rows four banks apart
 constexpr int kQkWaves = 8, kQkThreads = kQkWaves * kWave;
 constexpr int kQkKeys = kPiece / kQkWaves;  // keys of a piece per wave
@@ -1131,7 +1118,7 @@ hipError_t launch_fused_variant(const PlanView& p, const void* q, int ldq, const
     const int64_t g = (std::min(cap, limit) + kUnit - 1) / kUnit * kUnit;
     // Two wave pairs per item where one item's chain of chunks is what the launch waits
     // for: at least twenty chunks in the longest row and at most four items per CU (two
-    // sequences of 900..1024, 16 heads: 20.9 -> 16.2 us, masked 19.9 -> 14.3; but batch 32
+    // sequences of 900 and 1024, 16 heads: 19.9 -> 14.6 us, masked 19.1 -> 12.9; but batch 32
     // of 16..512, 1232 items, 17.2 -> 20.8: short items only pay for the merge).
     const bool split = p.max_len >= 640 && cap <= 4 * cus;
     auto* f = split ? &k_attention_bf16<CAUSAL, 2> : &k_attention_bf16<CAUSAL, 1>;

@@ -11,6 +11,7 @@ typedef __attribute__((ext_vector_type(4))) float floatx4;
 typedef __attribute__((ext_vector_type(16))) float floatx16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+typedef __attribute__((address_space(3))) void lds_void_t;
 
 constexpr int kWave = 64;
 constexpr int kTile = 64;     // attention tile edge (rows / cols of a score tile)
@@ -43,6 +44,16 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // Low / high bf16 halves of a packed pair, widened.
 __device__ __forceinline__ float lo_bf16(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float hi_bf16(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+
+// Workgroup-uniform values made so explicitly: the compiler cannot keep plan reads
+// in scalar registers where the same kernel may write the status word (atomicOr),
+// and a buffer descriptor built from a per-lane value becomes a per-lane loop.
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ int64_t uni64(int64_t v) {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
+    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(static_cast<uint64_t>(v) >> 32));
+    return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
+}
 
 // All-reduce within aligned groups of G lanes (a power of two), by moves inside the
 // vector unit: quad permutes and mirrors inside a row of 16 lanes, then lane swaps
@@ -126,9 +137,12 @@ __device__ __forceinline__ floatx4 mfma16x16x32(const bf16x8& a, const bf16x8& b
 
 // 32x32x16: lane l supplies row (l % 32) of A and column (l % 32) of B with the 8
 // k values 8*(l/32) .. 8*(l/32)+7; it receives C column l % 32, rows
-// 8*(r/4) + 4*(l/32) + (r%4) for accumulator element r = 0..15.  Measured on
-// MI355X, chains of this form sustain about 2.1 PFLOP/s against about 1.2 for
-// the 16x16x32 form, so the dense contractions use it.
+// 8*(r/4) + 4*(l/32) + (r%4) for accumulator element r = 0..15.  Which form is faster
+// depends on the operands, since the card is limited by power: chains on registers alone,
+// every SIMD at work, reach (TFLOP/s, 32x32x16 and 16x16x32) 2150-2420 and 1980-2200 at
+// one wave per SIMD with operands of zeros or ones, but 1680-1730 and 1770-1880 with
+// random ones; at two waves per SIMD 1640 and 2230-2330, random 1290-1400 and 1830.  The
+// 128 x 256 tiles and smaller ones use this form, the 256 x 256 tiles the other.
 __device__ __forceinline__ floatx16 mfma32x32x16(const bf16x8& a, const bf16x8& b, const floatx16& c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }

@@ -1,10 +1,10 @@
 // bf16 packed linear operator on 256 x 256 tiles (tokens x features): y = x w^T + bias +
 // residual for long reductions over enough of them.
-//  - What bounds it: power, then the loop's waits.  With random operands this card
-//    sustains 1950 TFLOP/s of v_mfma_f32_16x16x32_bf16 and 1750 of the 32x32x16 form (no
-//    memory traffic at all; the clock drops from 2.4 to 2.0 and 1.75 GHz), so every
-//    byte moved from L2 or LDS and the MFMA form itself cost rate.  A 256 x 256 tile
-//    moves 4 bytes per 512 products from L2 into LDS, a 128 x 256 tile 6.
+//  - What bounds it: power, then the loop's waits.  With random operands and two waves
+//    per SIMD this card sustains 1830 TFLOP/s of v_mfma_f32_16x16x32_bf16 and 1290 to 1400
+//    of the 32x32x16 form (no memory traffic at all; 2230 and 1640 with constant
+//    operands), so every byte moved from L2 or LDS and the MFMA form itself cost rate.  A
+//    256 x 256 tile moves 4 bytes per 512 products from L2 into LDS, a 128 x 256 tile 6.
 //  - Eight waves of 128 tokens x 64 features, one workgroup per CU; both operands staged 64
 //    k deep (128-byte rows, whole lines per copy request) in two stages of 64 KB.  The
 //    next 32-k group's fragments are read while a group's MFMAs run; before a step's last
@@ -13,8 +13,8 @@
 //  - One workgroup per CU leaves a tile's prologue and epilogue exposed, and a partial last
 //    round idle: its tiles run as four 128 x 128 quarters each (gemm_small_tile).
 // Against the 128 x 256 tiles (two workgroups per CU, 32x32x16 MFMAs): 35475 x 4096 x 1024
-// 294 -> 261 us, 20000 x 3072 x 768 85.4 -> 77.9, 8192^3 877 -> 807; but 35475 x 1024 x 4096
-// with GELU 291 -> 324, where sixteen steps do not pay for the exposed epilogue.
+// 281 -> 255 us, 20000 x 3072 x 768 83.3 -> 79.1, 8192^3 884 -> 829; but 35475 x 1024 x 4096
+// 270 -> 294, where sixteen steps do not pay for the exposed epilogue.
 #include <algorithm>
 
 #include "gemm_small_tile.h"

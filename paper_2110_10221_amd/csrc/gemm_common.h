@@ -8,8 +8,6 @@
 
 namespace rag {
 
-typedef __attribute__((address_space(3))) void lds_void_t;
-
 constexpr int kGroupM = 8;  // token tiles per group in the tile order
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
@@ -73,16 +71,6 @@ __device__ __forceinline__ bool trmm_tile_coords(int bid, int tiles_m, int tiles
 __device__ __forceinline__ int dealt_to_xcds(int p, int run) {
     const int xcd = p % 8, idx = p / 8;
     return ((idx / run) * 8 + xcd) * run + idx % run;
-}
-
-// Workgroup-uniform values made so explicitly: the compiler cannot keep plan reads
-// in scalar registers where the same kernel may write the status word (atomicOr),
-// and a buffer descriptor built from a per-lane value becomes a per-lane loop.
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ int64_t uni64(int64_t v) {
-    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
-    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(static_cast<uint64_t>(v) >> 32));
-    return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
 }
 
 // ---------------------------------------------------------------------------

@@ -93,11 +93,11 @@ hipError_t launch_small_act(int which, const LinearArgs& a, const PlanView* plan
 // One range apart: with more 128 x 128 tiles than CUs but no more of 128 x 256, the
 // latter all run at once in eight waves of 64 x 64, a CU each, with three 64-k stages.
 // Their fit grows with the share of CUs at work (the clock falls), and against the other
-// forms long reductions gain (10076 x 2048 x 512 32.8 -> 27.8 us, 7000 x 4096 x 1024 64.2
-// -> 59.4, 10076 x 3072 x 768 53.5 -> 47.5, 1500 x 1024 x 4096 20.6 -> 17.9), short ones
-// do not (14000 x 512 x 512 14.0 -> 14.4): one workgroup per CU hides neither its first
-// loads nor its epilogue.  Nor where two rounds of 64 x 128 are all there is to do
-// (1310 x 1024 x 3072 12.8 -> 16.0), which the estimates show.
+// forms long reductions gain (best of them -> this, 10076 x 2048 x 512 30.8 -> 26.7 us,
+// 7000 x 4096 x 1024 60.5 -> 55.8, 10076 x 3072 x 768 49.5 -> 45.4, 1500 x 1024 x 4096 18.4
+// -> 17.2), short ones do not (14000 x 512 x 512 12.0 -> 12.4): one workgroup per CU hides
+// neither its first loads nor its epilogue.  Nor where two rounds of 64 x 128 are all there
+// is to do (1310 x 1024 x 3072 12.5 -> 16.1), which the estimates show.
 static int small_gemm_choice(int64_t T, int64_t K, int64_t N, bool residual, int64_t cus) {
     struct Form {
         int64_t tm, tn;
