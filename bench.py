@@ -564,8 +564,8 @@ def vgemm_measurement(rag, batch=128, iters=20):
     alg_bytes = 2.0 * (a_n + b_n + c_n)
     return {"workload": f"vgemm, batch {batch}, m n k uniform over multiples of 128 in [512, 1408] (seed {batch})",
             "ms": round(ms, 4), "useful_tflops": round(tf, 1), "frac_of_bf16_peak": round(tf / PEAK_BF16_TFLOPS, 4),
-            "kernel": "k_vgemm_bf16", "tiles": plan.n_tiles(), "plan_ms": round(ms_plan, 4),
-            "algorithmic_bytes": alg_bytes, "hbm_bytes_per_launch": load_traffic("k_vgemm_bf16"),
+            "kernel": "k_vgemm_bf16<false>", "tiles": plan.n_tiles(), "plan_ms": round(ms_plan, 4),
+            "algorithmic_bytes": alg_bytes, "hbm_bytes_per_launch": load_traffic("k_vgemm_bf16<false>"),
             "padded_bmm_ms": round(ms_pad, 4), "speedup_vs_padded_bmm": round(ms_pad / ms, 3),
             "per_problem_matmul_ms": round(ms_loop, 4), "speedup_vs_per_problem_matmul": round(ms_loop / ms, 3),
             "useful_fraction_of_padded": round(useful / (2.0 * batch * M * N * K), 4),
