@@ -1,16 +1,17 @@
 // Ragged scaled dot-product attention over the plan's work lists: the paper's
 // QK^T, Softmax and AttnV operators one by one, and the three fused.
-//   ragged QK^T     bf16: one workgroup item = one (sequence, head, 64-query
-//                   block), walking every 64-key tile of its rows; fp32: one
+//   ragged QK^T     bf16: one workgroup item = one (sequence, 64-query block,
+//                   group of heads), walking all keys of its rows; fp32: one
 //                   item = one 64x64 score tile.  No tile crosses a sequence
 //                   boundary, so no padded work is done beyond predicated edges
 //   ragged softmax  one wave per token (or group of its heads): the token's H rows
 //                   (each L_b scores) are contiguous in the X[b][i][h][j] layout
-//   ragged Attn.V   one workgroup item = 64 query rows of one sequence and head,
-//                   reducing over that sequence's L_b keys
+//   ragged Attn.V   one workgroup item = 64 query rows of one sequence and head
+//                   (bf16: group of heads), reducing over that sequence's L_b keys
 //   fused           one (sequence, head, 64-query tile) item per two-wave
 //                   workgroup, keys streamed through LDS (details further down)
-// The operators' persistent grids walk the lists in order: sequences longest first.
+// The persistent grids of QK^T and Attn.V walk the lists in order: sequences longest
+// first.
 //
 // The unfused bf16 kernels use v_mfma_f32_16x16x32_bf16.  In a 16x16x32 MFMA lane l
 // supplies row (l % 16) of A and column (l % 16) of B, each with the 8 consecutive
@@ -712,9 +713,10 @@ __global__ __launch_bounds__(256) void k_attn_v_f32(PlanArgs pa, const float* __
 // longest sequence first (the plan's order).
 //   keys   stream through two LDS stages of 32 K rows and 32 V rows (16 KB per
 //          workgroup, so eight workgroups share a CU: while one waits for its
-//          next chunk the others compute, and every SIMD keeps four busy waves
-//          whatever the lengths); bounds-checked buffer loads write LDS
-//          directly, 16-byte chunks XOR-swizzled by row, rows past L_b as zeros
+//          next chunk the others compute, and in a launch of eight items per CU
+//          or more every SIMD keeps four busy waves whatever the lengths);
+//          bounds-checked buffer loads write LDS directly, 16-byte chunks
+//          XOR-swizzled by row, rows past L_b as zeros
 //   scores S^T = K Q^T with v_mfma_f32_32x32x16_bf16 (lane holds query
 //          i = lane % 32 and keys 8*(r/4) + 4*(lane/32) + r%4), kept in fp32
 //   softmax online: z = s * scale * log2(e); a per-row reference m, the
